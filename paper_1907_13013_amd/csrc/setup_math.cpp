@@ -3,6 +3,7 @@
 // Fokker-Planck operator.  See setup_math.hpp for the formulation.
 #include "setup_math.hpp"
 
+#include <algorithm>
 #include <cmath>
 #include <map>
 #include <stdexcept>
@@ -150,7 +151,7 @@ dvec mpd_laplacian(int N, const dvec &mu, const dvec &w) {
 
 bool build_fp_factors(int K, int N, int L, const double *h, const double *sigma_t,
                       const double *sigma_s, const dvec &mu, const dvec &w, const dvec &A,
-                      FPFactors &out, int chunk_hint) {
+                      FPFactors &out, int chunk_hint, int tree_slabs) {
     const int L1 = L + 1;
     dvec sa(K), str(K);
     for (int j = 0; j < K; ++j) {
@@ -158,12 +159,14 @@ bool build_fp_factors(int K, int N, int L, const double *h, const double *sigma_
         sa[j] = sigma_t[j] - ss[0];
         str[j] = ss[0] - (L1 > 1 ? ss[1] : 0.0);
     }
-    return build_fp_factors_coef(K, N, L, h, sa.data(), str.data(), sigma_s, mu, w, A, out, chunk_hint);
+    return build_fp_factors_coef(K, N, L, h, sa.data(), str.data(), sigma_s, mu, w, A, out, chunk_hint, tree_slabs);
 }
 
-bool build_fp_factors_coef(int K, int N, int L, const double *h, const double *sigma_a,
-                           const double *sigma_tr, const double *sigma_s, const dvec &mu, const dvec &w,
-                           const dvec &A, FPFactors &out, int chunk_hint) {
+// Cell types and their maps: the interface responses T, R, R', T' of each
+// type (into ct) and its source and moment maps (into out).
+static bool fp_cell_types(int K, int N, int L, const double *h, const double *sigma_a, const double *sigma_tr,
+                          const double *sigma_s, const dvec &mu, const dvec &w, const dvec &A, FPFactors &out,
+                          FPCellTypes &ct) {
     const int NH = N / 2, N2 = 2 * N, L1 = L + 1, L2 = 2 * L1;
     out.K = K; out.N = N; out.L = L; out.NH = NH;
     out.folded_sigma_s = sigma_s != nullptr;
@@ -175,7 +178,8 @@ bool build_fp_factors_coef(int K, int N, int L, const double *h, const double *s
     std::vector<std::vector<double>> keys;
     out.seg_begin.clear();
     out.seg_type.clear();
-    std::vector<int> cell_type(K);
+    std::vector<int> &cell_type = ct.cell_type;
+    cell_type.assign(K, 0);
     const int nkey = 3 + (sigma_s ? L1 : 0);
     for (int j = 0; j < K; ++j) {
         std::vector<double> key(nkey);
@@ -204,7 +208,8 @@ bool build_fp_factors_coef(int K, int N, int L, const double *h, const double *s
     out.ntypes = ntypes;
 
     // ---- per type: cell block, responses, source and moment maps
-    std::vector<dvec> Tc(ntypes), Rc(ntypes), Rpc(ntypes), Tpc(ntypes);
+    std::vector<dvec> &Tc = ct.T, &Rc = ct.R, &Rpc = ct.Rp, &Tpc = ct.Tp;
+    for (std::vector<dvec> *v : {&Tc, &Rc, &Rpc, &Tpc}) v->assign(ntypes, dvec());
     out.EsrcT.assign((size_t)ntypes * L2 * N, 0.0);
     out.PhisrcT.assign((size_t)ntypes * L2 * L2, 0.0);
     out.PhiinfT.assign((size_t)ntypes * N * L2, 0.0);
@@ -291,6 +296,27 @@ bool build_fp_factors_coef(int K, int N, int L, const double *h, const double *s
             }
     }
 
+    return true;
+}
+
+bool build_fp_factors_coef(int K, int N, int L, const double *h, const double *sigma_a,
+                           const double *sigma_tr, const double *sigma_s, const dvec &mu, const dvec &w,
+                           const dvec &A, FPFactors &out, int chunk_hint, int tree_slabs) {
+    FPCellTypes ct;
+    if (!fp_cell_types(K, N, L, h, sigma_a, sigma_tr, sigma_s, mu, w, A, out, ct)) return false;
+    const int NH = N / 2;
+    const std::vector<int> &cell_type = ct.cell_type;
+    const std::vector<dvec> &Tc = ct.T, &Rc = ct.R, &Rpc = ct.Rp, &Tpc = ct.Tp;
+    // chunk length ~ sqrt(K/2) balances the local pass (chunk steps) against
+    // the fix pass (up to K/chunk fold steps + chunk steps)
+    int chunk = chunk_hint > 0 ? chunk_hint : (int)std::lround(std::sqrt(0.5 * K));
+    if (chunk < 4) chunk = 4;
+    if (chunk > K) chunk = K;
+    out.chunk = chunk;
+    out.nchunks = (K + chunk - 1) / chunk;
+    if (tree_slabs > 0 && build_fp_tree(K, N, L, tree_slabs, ct, out, out.tree)) return true;
+    out.tree = FPTree();
+
     // ---- Riccati eliminations from both faces
     const size_t M2 = (size_t)NH * NH;
     const size_t CM = FP_CELL_MATS * M2;
@@ -335,13 +361,6 @@ bool build_fp_factors_coef(int K, int N, int L, const double *h, const double *s
     }
 
     // ---- chunk products for the chunked recurrences
-    // chunk length ~ sqrt(K/2) balances the local pass (chunk steps) against
-    // the fix pass (up to K/chunk fold steps + chunk steps)
-    int chunk = chunk_hint > 0 ? chunk_hint : (int)std::lround(std::sqrt(0.5 * K));
-    if (chunk < 4) chunk = 4;
-    if (chunk > K) chunk = K;
-    out.chunk = chunk;
-    out.nchunks = (K + chunk - 1) / chunk;
     out.chunk_fwd.assign((size_t)out.nchunks * M2, 0.0);
     out.chunk_bwd.assign((size_t)out.nchunks * M2, 0.0);
     for (int c = 0; c < out.nchunks; ++c) {
@@ -418,6 +437,372 @@ bool build_fp_factors_coef(int K, int N, int L, const double *h, const double *s
         }
     }
     return true;
+}
+
+// ---------------------------------------------------------------------------
+// Doubling tree (see FPTree)
+// ---------------------------------------------------------------------------
+
+int fp_tree_nb(int N) {
+    int best = 2, pad = 0;
+    for (int nb = 2; nb <= 8; nb *= 2) {
+        const int p = (N + 4 * nb - 1) / (4 * nb) * (4 * nb);
+        if (nb == 2) pad = p;
+        if (p <= pad + pad / 7) best = nb;
+    }
+    return best;
+}
+size_t fp_tree_ld(int N, int cols) {
+    const int kb = 4 * fp_tree_nb(N);
+    return (size_t)(cols + kb - 1) / kb * kb + 1;
+}
+
+dvec fp_tree_fragments(const double *B, int K, int cols, int nb) {
+    const int KS = (K + 4 * nb - 1) / (4 * nb) * nb, CT = (cols + 15) / 16;
+    dvec out((size_t)CT * KS * 64, 0.0);
+    for (int c = 0; c < CT; ++c)
+        for (int p = 0; p < KS / 2; ++p)
+            for (int l = 0; l < 64; ++l)
+                for (int e = 0; e < 2; ++e) {
+                    const int k = 8 * p + 4 * e + l / 16, col = 16 * c + l % 16;
+                    if (k < K && col < cols)
+                        out[(((size_t)c * (KS / 2) + p) * 64 + l) * 2 + e] = B[(size_t)k * cols + col];
+                }
+    return out;
+}
+
+// doubles of LDS of a chunk of c leaves: interface rows, the second set of
+// rows of a root chunk, and the moment-difference rows of a leaf stage
+static size_t tree_lds(int N, int L2, int c, bool leaf, bool root) {
+    return (size_t)(root ? 2 : 1) * (c + 1) * fp_tree_ld(N, N) + (leaf ? (size_t)c * fp_tree_ld(N, L2) : 0);
+}
+
+// Fragments and per-wave unit lists of a built tree.
+static bool tree_records(int N, int L2, const FPFactors &maps, FPTree &out) {
+    const int nb = fp_tree_nb(N), nt = maps.ntypes;
+    const int ksN = (N + 4 * nb - 1) / (4 * nb) * nb, ksL = (L2 + 4 * nb - 1) / (4 * nb) * nb;
+    const int ctN = (N + 15) / 16, ctU = (2 * N + 15) / 16, ctL = (L2 + 15) / 16;
+    // fragment offsets, in blocks of 64 doubles
+    const size_t up = (size_t)ctU * ksN, dn = (size_t)ctN * ksN;
+    const size_t src0 = (size_t)out.nclasses * (up + dn), upd0 = src0 + (size_t)nt * ctN * ksL;
+    const size_t inf0 = upd0 + (size_t)nt * ctL * ksL, all = inf0 + (size_t)nt * ctL * ksN;
+    if (all > 0x7fffffffu) return false;
+    out.frag.clear();
+    out.frag.reserve(all * 64);
+    auto put = [&](const double *B, int K, int cols) {
+        const dvec v = fp_tree_fragments(B, K, cols, nb);
+        out.frag.insert(out.frag.end(), v.begin(), v.end());
+    };
+    const size_t N2 = (size_t)N * N;
+    for (int k = 0; k < out.nclasses; ++k) {
+        put(&out.mats[k * 3 * N2], N, 2 * N);
+        put(&out.mats[k * 3 * N2 + 2 * N2], N, N);
+    }
+    for (int t = 0; t < nt; ++t) put(&maps.EsrcT[(size_t)t * L2 * N], L2, N);
+    for (int t = 0; t < nt; ++t) put(&maps.PhisrcT[(size_t)t * L2 * L2], L2, L2);
+    for (int t = 0; t < nt; ++t) put(&maps.PhiinfT[(size_t)t * N * L2], N, L2);
+    for (FPTreeStage &s : out.stages) {
+        std::vector<std::vector<int>> recs((size_t)s.chunks * kTreeWaves);
+        size_t most = 0;
+        for (int p = 0; p < s.chunks; ++p) {
+            const int *lv = &out.lv[(size_t)out.chunk_list[s.first_chunk + p] * kTreeLv];
+            for (int w = 0; w < kTreeWaves; ++w) {
+                std::vector<int> ends, units;
+                // the units (pass, column tile) of a phase, dealt to the waves in turn
+                auto phase = [&](int l, int ct, auto &&offset, int entries) {
+                    int u = 0;
+                    for (int q = lv[l]; q < lv[l + 1]; ++q)
+                        for (int c = 0; c < ct; ++c, ++u) {
+                            if (u % kTreeWaves != w) continue;
+                            const FPPass &ps = out.passes[q];
+                            for (int e = 0; e < entries; ++e) {
+                                units.push_back((int)offset(ps.cls, c, e));
+                                units.push_back(ps.first | (ps.rows << 8) | (c << 16));
+                            }
+                        }
+                    ends.push_back((int)units.size() / 2);
+                };
+                if (s.leaf)
+                    phase(0, ctN, [&](int cls, int c, int) { return src0 + ((size_t)cls * ctN + c) * ksL; }, 1);
+                else
+                    ends.push_back(0);
+                for (int l = 1; l <= s.levels; ++l)
+                    phase(l, ctU, [&](int cls, int c, int) { return cls * (up + dn) + (size_t)c * ksN; }, 1);
+                for (int l = s.levels; l >= 1; --l)
+                    phase(l, ctN, [&](int cls, int c, int) { return cls * (up + dn) + up + (size_t)c * ksN; }, 1);
+                if (s.leaf)
+                    phase(0, ctL, [&](int cls, int c, int e) {
+                        return e == 0 ? upd0 + ((size_t)cls * ctL + c) * ksL : inf0 + ((size_t)cls * ctL + c) * ksN;
+                    }, 2);
+                else
+                    ends.push_back((int)units.size() / 2);
+                if (units.empty()) units = {0, 1 << 8};
+                // one more entry, so that the last unit has a successor to request
+                units.push_back(units[units.size() - 2]);
+                units.push_back(units[units.size() - 2]);
+                if ((int)ends.size() > kTreeHdr || units.size() / 2 > (size_t)kTreeMaxUnits) return false;
+                std::vector<int> &r = recs[(size_t)p * kTreeWaves + w];
+                for (int i = 0; i < kTreeHdr; ++i) r.push_back(ends[std::min<size_t>(i, ends.size() - 1)]);
+                r.insert(r.end(), units.begin(), units.end());
+                most = std::max(most, units.size());
+            }
+        }
+        s.rec_stride = kTreeHdr + (int)most;
+        s.rec0 = out.records.size();
+        out.records.resize(s.rec0 + recs.size() * s.rec_stride, 0);
+        for (size_t i = 0; i < recs.size(); ++i)
+            std::copy(recs[i].begin(), recs[i].end(), out.records.begin() + s.rec0 + i * s.rec_stride);
+    }
+    return true;
+}
+
+// Cuts the levels into stages.  cls0: the cells' types, icls[l]: the classes
+// of level l's interfaces.
+static bool tree_stages(int K, int N, int L2, int slabs, const std::vector<int> &cls0,
+                        const std::vector<std::vector<int>> &icls, FPTree &out) {
+    const int nb = fp_tree_nb(N), top = (int)icls.size() - 1;
+    const int ksN = (N + 4 * nb - 1) / (4 * nb) * nb, ksL = (L2 + 4 * nb - 1) / (4 * nb) * nb;
+    const int ctN = (N + 15) / 16, ctU = (2 * N + 15) / 16, ctL = (L2 + 15) / 16;
+    // a product of so many rows with ct column tiles over ks k-steps
+    auto product = [](int rows, int ct, int ks) {
+        const double mfma = (double)ct * ks * (rows > 8 ? 150 : rows > 4 ? 60 : 40) * kTreeUsPerMfmaClk;
+        return std::max(mfma, (double)ct * ks * 64 * 8 * kTreeUsPerByte);
+    };
+    // one launch's time over levels lo + 1 .. hi: the longest chunk, times the
+    // rounds of blocks when there are more chunks than CUs; < 0: not possible
+    auto stage = [&](int lo, int hi) -> double {
+        const bool leaf = lo == 0, root = hi == top;
+        const int n = (int)(((size_t)K + ((size_t)1 << lo) - 1) >> lo), c = 1 << (hi - lo);
+        const int chunks = (n + c - 1) / c, rows = std::min(c, n);
+        if (rows > kTreeMaxRows || 2 * (hi - lo) + 2 > kTreeHdr) return -1.0;
+        if (tree_lds(N, L2, rows, leaf, root) * sizeof(double) > kTreeLdsBytes) return -1.0;
+        double up = 0.0, down = 0.0, whole = 0.0;
+        for (int p = 0; p < chunks; ++p) {
+            double u = 0.0, d = 0.0;
+            int units = 0, passes = 0;
+            auto level = [&](const std::vector<int> &cls, int i0, int i1, auto &&add) {
+                for (int i = i0; i < i1;) {
+                    int e = i + 1;
+                    while (e < i1 && e - i < 16 && cls[e] == cls[i]) ++e;
+                    add(e - i);
+                    ++passes;
+                    i = e;
+                }
+            };
+            for (int l = leaf ? 0 : lo + 1; l <= hi; ++l) {
+                const size_t per = (size_t)1 << (hi - l), all = l ? icls[l].size() : cls0.size();
+                const std::vector<int> &cls = l ? icls[l] : cls0;
+                const int i0 = (int)std::min(all, p * per);
+                int i1 = (int)std::min(all, (p + 1) * per);
+                if (l && i1 > i0 && cls[i1 - 1] < 0) --i1;  // the last node has one child
+                u += kTreeUsPerLevel;
+                d += kTreeUsPerLevel;
+                level(cls, i0, i1, [&](int r) {
+                    u += l ? product(r, ctU, ksN) : product(r, ctN, ksL);
+                    d += l ? product(r, ctN, ksN) : product(r, ctL, ksL + ksN);
+                    units += l ? ctU + ctN : ctN + 2 * ctL;
+                });
+            }
+            if (passes > kTreeMaxPasses || (units + 7 * (2 * (hi - lo) + 2)) / kTreeWaves + 2 > kTreeMaxUnits) return -1.0;
+            up = std::max(up, u);
+            down = std::max(down, d);
+            whole = std::max(whole, u + d);
+        }
+        const double rows_us = (double)rows * (N + (leaf ? 2 * L2 : 0)) * 8 * kTreeUsPerByte;
+        const double rounds = std::max(1.0, (double)chunks * slabs / kTreeCus);
+        return root ? kTreeUsPerLaunch + rounds * (whole + rows_us)
+                    : 2 * kTreeUsPerLaunch + rounds * (up + down + 2 * rows_us);
+    };
+    // best[s][lo]: the levels above lo in at most s + 1 stages, the next one up to cut[s][lo]
+    std::vector<std::vector<double>> best(kTreeMaxStages, std::vector<double>(top + 1, -1.0));
+    std::vector<std::vector<int>> cut(kTreeMaxStages, std::vector<int>(top + 1, top));
+    // (at least two levels a stage: the later stages' interfaces fit the work array)
+    for (int lo = top ? top - 1 : 0; lo >= 0; --lo)
+        for (int hi = std::min(top, lo + 2); hi <= std::min(top, lo + kTreeMaxLevels); ++hi) {
+            const double t = stage(lo, hi);
+            if (t < 0.0) continue;
+            for (int s = 0; s < kTreeMaxStages; ++s) {
+                if (hi < top && (s == 0 || best[s - 1][hi] < 0.0)) continue;
+                const double all = t + (hi < top ? best[s - 1][hi] : 0.0);
+                if (best[s][lo] < 0.0 || all < best[s][lo]) {
+                    best[s][lo] = all;
+                    cut[s][lo] = hi;
+                }
+            }
+        }
+    if (best[kTreeMaxStages - 1][0] < 0.0) return false;
+    size_t later = 0;
+    for (int lo = 0, s = kTreeMaxStages - 1;; --s) {
+        FPTreeStage g;
+        const int hi = cut[s][lo];
+        g.n = (int)(((size_t)K + ((size_t)1 << lo) - 1) >> lo);
+        g.leaf = lo == 0;
+        g.levels = hi - lo;
+        g.c = 1 << g.levels;
+        g.chunks = (g.n + g.c - 1) / g.c;
+        if (lo) later += (size_t)(g.n + 1) * N;
+        out.stages.push_back(g);
+        lo = hi;
+        if (hi == top) break;
+    }
+    // the later stages' interfaces share one (K + 1) N / 2 work array
+    return later <= (size_t)(K + 1) * (N / 2);
+}
+
+bool build_fp_tree(int K, int N, int L, int slabs, const FPCellTypes &ct, const FPFactors &maps, FPTree &out) {
+    const int NH = N / 2, L2 = 2 * (L + 1);
+    const size_t M2 = (size_t)NH * NH, N2 = (size_t)N * N;
+    out = FPTree();
+    const int ntypes = (int)ct.T.size();
+    // Widths up to 128 past 96 and few types: the eliminations, one launch a
+    // type on all CUs where a level here is one CU's stream of matrices.
+    // us a correction, eliminations / tree, N = 128: K = 240 with 1, 2, 3, 4
+    // and 6 types 69 / 78, 84 / 112, 106 / 108, 127 / 107, 168 / 114; one type
+    // and K = 40, 120, 500, 700, 1000 62 / 47, 66 / 78, 78 / 96, 87 / 100,
+    // 120 / 106.  Elsewhere the tree: K = 240, N = 112, 160 and 192 76 / 74,
+    // 222 / 133 and 252 / 163; K = 2000, N = 64 57 / 48; K = 2000, N = 64 and
+    // 200, 700, 2000 types 2510 / 97, 9000 / 146, 25000 / 197.
+    if (N > 112 && N <= 128 && ntypes <= 3 && K > 64 && K < 900) return false;
+    // node classes: operators (T, R, R', T') per class, classes of equal
+    // child pairs shared
+    struct Node {
+        dvec T, R, Rp, Tp;
+    };
+    std::vector<Node> ops;
+    for (int t = 0; t < ntypes; ++t) ops.push_back(Node{ct.T[t], ct.R[t], ct.Rp[t], ct.Tp[t]});
+    std::map<std::pair<int, int>, int> pair_of;  // (left, right) -> node class
+    std::map<std::vector<int>, int> list_of;
+    dvec X(M2), t0(M2), t1(M2), t2(M2), t3(M2);
+    auto combine = [&](int a, int b) -> int {
+        auto it = pair_of.find({a, b});
+        if (it != pair_of.end()) return it->second;
+        Node nw;
+        for (dvec *v : {&nw.T, &nw.R, &nw.Rp, &nw.Tp}) v->assign(M2, 0.0);
+        const Node &A = ops[a], &B = ops[b];
+        // X = (I - R_A R'_B)^{-1}
+        matmul(NH, NH, NH, A.R.data(), B.Rp.data(), t0.data());
+        for (size_t e = 0; e < M2; ++e) X[e] = -t0[e];
+        for (int i = 0; i < NH; ++i) X[(size_t)i * NH + i] += 1.0;
+        if (!invert(NH, X.data())) return -1;
+        // M1 = [[X, X R_A], [R'_B X, I + R'_B X R_A]]
+        dvec XR(M2), RX(M2), RXR(M2);
+        matmul(NH, NH, NH, X.data(), A.R.data(), XR.data());
+        matmul(NH, NH, NH, B.Rp.data(), X.data(), RX.data());
+        matmul(NH, NH, NH, RX.data(), A.R.data(), RXR.data());
+        for (int i = 0; i < NH; ++i) RXR[(size_t)i * NH + i] += 1.0;
+        // right operands: up [N][2N] = [M1^T | (diag(T_B, T'_A) M1)^T], down [N][N] = (M1 diag(T_A, T'_B))^T
+        const size_t base = out.mats.size();
+        out.mats.resize(base + 3 * N2);
+        double *U = &out.mats[base], *D = U + 2 * N2;
+        auto put_up = [&](const dvec &M, int r0, int c0, int off) {  // rows r0.. of M1 block at columns c0..
+            for (int r = 0; r < NH; ++r)
+                for (int c = 0; c < NH; ++c) U[(size_t)(c0 + c) * 2 * N + off + r0 + r] = M[(size_t)r * NH + c];
+        };
+        put_up(X, 0, 0, 0);
+        put_up(XR, 0, NH, 0);
+        put_up(RX, NH, 0, 0);
+        put_up(RXR, NH, NH, 0);
+        dvec P(M2);
+        auto put_dn = [&](const dvec &M, int r0, int c0) {
+            for (int r = 0; r < NH; ++r)
+                for (int c = 0; c < NH; ++c) D[(size_t)(c0 + c) * N + r0 + r] = M[(size_t)r * NH + c];
+        };
+        matmul(NH, NH, NH, B.T.data(), X.data(), t0.data());     // T_B X
+        put_up(t0, 0, 0, N);
+        matmul(NH, NH, NH, B.T.data(), XR.data(), P.data());     // T_B X R_A
+        put_up(P, 0, NH, N);
+        matmul(NH, NH, NH, A.Tp.data(), RX.data(), t1.data());   // T'_A R'_B X
+        put_up(t1, NH, 0, N);
+        matmul(NH, NH, NH, A.Tp.data(), RXR.data(), t2.data());  // T'_A (I + R'_B X R_A)
+        put_up(t2, NH, NH, N);
+        // the node's operators
+        matmul(NH, NH, NH, t0.data(), A.T.data(), nw.T.data());
+        matmul(NH, NH, NH, P.data(), B.Tp.data(), t3.data());
+        for (size_t e = 0; e < M2; ++e) nw.R[e] = B.R[e] + t3[e];
+        matmul(NH, NH, NH, t1.data(), A.T.data(), t3.data());
+        for (size_t e = 0; e < M2; ++e) nw.Rp[e] = A.Rp[e] + t3[e];
+        matmul(NH, NH, NH, t2.data(), B.Tp.data(), nw.Tp.data());
+        matmul(NH, NH, NH, X.data(), A.T.data(), P.data());
+        put_dn(P, 0, 0);
+        matmul(NH, NH, NH, XR.data(), B.Tp.data(), P.data());
+        put_dn(P, 0, NH);
+        matmul(NH, NH, NH, RX.data(), A.T.data(), P.data());
+        put_dn(P, NH, 0);
+        matmul(NH, NH, NH, RXR.data(), B.Tp.data(), P.data());
+        put_dn(P, NH, NH);
+        ops.push_back(std::move(nw));
+        const int id = (int)ops.size() - 1;
+        pair_of.emplace(std::make_pair(a, b), id);
+        return id;
+    };
+    // class of the interface inside each node, level by level (icls[l][i]);
+    // the node classes of level l are cls_at[l]
+    int top = 0;
+    while (((size_t)1 << top) < (size_t)K) ++top;
+    std::vector<std::vector<int>> icls(top + 1), cls_at(top + 1);
+    cls_at[0] = ct.cell_type;
+    for (int l = 1; l <= top; ++l) {
+        const std::vector<int> &cur = cls_at[l - 1];
+        const int m = (int)cur.size();
+        std::vector<int> &up = cls_at[l];
+        up.assign((m + 1) / 2, 0);
+        icls[l].assign((m + 1) / 2, -1);
+        for (int i = 0; i < (m + 1) / 2; ++i) {
+            if (2 * i + 1 < m) {
+                const int id = combine(cur[2 * i], cur[2 * i + 1]);
+                if (id < 0) return false;
+                up[i] = id;
+                icls[l][i] = id - ntypes;
+            } else {
+                up[i] = cur[2 * i];
+            }
+        }
+    }
+    if (!tree_stages(K, N, L2, slabs, cls_at[0], icls, out)) return false;
+    int lo = 0;
+    for (FPTreeStage &s : out.stages) {
+        const int n = s.n;
+        // passes per chunk: runs of at most 16 rows of one class, by level
+        // (level 0: the leaf cells by type)
+        s.first_chunk = (int)out.chunk_list.size();
+        for (int p = 0; p < s.chunks; ++p) {
+            const int c0 = p * s.c, nc = std::min(s.c, n - c0);
+            std::vector<int> key;
+            std::vector<FPPass> ps;
+            std::vector<int> lv;
+            for (int l = 0; l <= s.levels; ++l) {
+                lv.push_back((int)ps.size());
+                if (l == 0 && !s.leaf) continue;
+                const int half = l ? 1 << (l - 1) : 0, step = 1 << l;
+                for (int r = 0; half + step * r < nc; ++r) {
+                    const int c = l ? icls[lo + l][(c0 >> l) + r] : cls_at[0][c0 + r];
+                    if ((int)ps.size() > lv[l] && ps.back().cls == c && ps.back().rows < 16)
+                        ++ps.back().rows;
+                    else
+                        ps.push_back(FPPass{(short)r, 1, c});
+                }
+            }
+            lv.push_back((int)ps.size());
+            if (ps.size() > (size_t)kTreeMaxPasses) return false;
+            for (const FPPass &q : ps) {
+                key.push_back(q.first);
+                key.push_back(q.rows);
+                key.push_back(q.cls);
+            }
+            key.insert(key.end(), lv.begin(), lv.end());
+            auto it = list_of.find(key);
+            if (it == list_of.end()) {
+                it = list_of.emplace(key, (int)list_of.size()).first;
+                const int base = (int)out.passes.size();
+                out.passes.insert(out.passes.end(), ps.begin(), ps.end());
+                for (int l = 0; l < kTreeLv; ++l) out.lv.push_back(base + lv[std::min<size_t>(l, lv.size() - 1)]);
+            }
+            out.chunk_list.push_back(it->second);
+        }
+        lo += s.levels;  // the chunks are the next stage's leaves
+    }
+    out.nclasses = (int)pair_of.size();
+    return tree_records(N, L2, maps, out);
 }
 
 }  // namespace snfpsa

@@ -4,6 +4,7 @@
 // excludes this setup from its solver timings, Sec. 4).
 #pragma once
 
+#include <cstddef>
 #include <cstdint>
 #include <vector>
 
@@ -47,6 +48,78 @@ dvec mpd_laplacian(int N, const dvec &mu, const dvec &w);
 // vectors change per application.
 constexpr int FP_CELL_MATS = 7;  // per cell: G, Hm, Gb, Hb, W, W rho, sig
 
+// Doubling tree.  The interface relations of a
+// run of cells compose like those of one cell: for neighbouring runs A, B
+// with responses (T, R, R', T') and outgoing sources (s+, s-) under zero
+// inflow, the interface between them carries
+//   [a; b] = M1 [s+_A; s-_B] + M1 diag(T_A, T'_B) [a_in; b_in],
+//   M1 = [[X, X R_A], [R'_B X, I + R'_B X R_A]],  X = (I - R_A R'_B)^{-1},
+// and the pair's outgoing sources are s+_B + T_B a and s-_A + T'_A b (zero
+// inflow).  Going up a binary tree over the cells gives every interface's
+// zero-inflow value and the slab's outgoing flux, going down adds each
+// node's inflow.  Nodes with equal children share their matrices, so a slab
+// of one cell type needs about two matrix sets per level where the
+// eliminations above need nine N/2 x N/2 matrices per cell, and every level
+// is a product of all its interfaces' rows with shared matrices (a slab whose
+// cells all differ has a matrix set per node: three N x N).  The dependent
+// chain is two products a level where the eliminations' is sqrt(K) steps, and
+// every launch takes all cell types at once.
+//
+// The tree is cut into stages of chunks (c leaves each, a power of two): a
+// chunk goes up its levels on its own, the chunks are the next stage's
+// leaves, and the last stage is one chunk (the root).  The cut is the one of
+// the least predicted time (kTreeUs...): short chunks spread the levels over
+// the CUs, long ones save launches, and each level of a chunk streams its
+// classes' matrices into one CU.
+struct FPCellTypes {
+    std::vector<int> cell_type;
+    std::vector<dvec> T, R, Rp, Tp;   // [ntypes] NH x NH interface responses
+};
+// Work of one chunk: at level l (0: the leaf cells), `rows` rows from row
+// `first` on take the matrices of class (level 0: cell type) cls.  Row i of
+// level l is the interface 2^(l-1) + 2^l i of the chunk.
+struct FPPass {
+    short first, rows;
+    int cls;
+};
+struct FPTreeStage {
+    int n = 0, c = 0, chunks = 0, levels = 0, leaf = 0;
+    int first_chunk = 0;              // into FPTree::chunk_list
+    size_t rec0 = 0;                  // the stage's records (FPTree::records), ints
+    int rec_stride = 0;
+};
+constexpr int kTreeMaxStages = 5, kTreeLv = 12, kTreeMaxPasses = 128;
+constexpr int kTreeWaves = 8;         // waves of a chunk's block
+constexpr int kTreeHdr = 20, kTreeMaxUnits = 128;
+constexpr int kTreeMaxRows = 255, kTreeMaxLevels = 8;
+constexpr size_t kTreeLdsBytes = 148 << 10;
+// Cost model of the cut into stages (microseconds): a launch with its gap, a
+// level's barriers and bookkeeping, a byte of matrices into one CU (measured
+// 100 to 134 GB/s), a cycle of FP64 MFMA on one of a CU's four SIMDs at 2.39 GHz.
+constexpr double kTreeUsPerLaunch = 4.5, kTreeUsPerLevel = 0.7, kTreeUsPerByte = 1.0 / 110e3,
+                 kTreeUsPerMfmaClk = 1.0 / (4 * 2390.0);
+constexpr int kTreeCus = 256;
+struct FPTree {
+    std::vector<FPTreeStage> stages;  // empty: no tree
+    int nclasses = 0;
+    dvec mats;                        // [nclasses]: up [N][2N], then down [N][N]
+    std::vector<FPPass> passes;
+    std::vector<int> lv;              // [lists][kTreeLv] first pass of each level
+    std::vector<int> chunk_list;      // per stage and chunk: its list
+    // right operands in the kernels' fragment order: per class up [N][2N] and
+    // down [N][N], then per cell type the source, moment and inflow maps
+    dvec frag;
+    // per stage, chunk and wave: the ends of the wave's units by phase (cells,
+    // up 1 .. levels, down levels .. 1, update; kTreeHdr ints), then the
+    // units (fragment offset in 64 doubles, first row | rows << 8 | column
+    // tile << 16), one unit (pass, column tile) after the other
+    std::vector<int> records;
+};
+int fp_tree_nb(int N);                // k-steps of 4 per batch of right operands
+size_t fp_tree_ld(int N, int cols);   // LDS row stride of left operands of so many columns
+// [K][cols] in the kernels' fragment order (see FPTreeArgs)
+dvec fp_tree_fragments(const double *B, int K, int cols, int nb);
+
 struct FPFactors {
     int K = 0, N = 0, L = 0, NH = 0;
     int chunk = 0, nchunks = 0;
@@ -77,15 +150,23 @@ struct FPFactors {
     //   PhisrcT[2(L+1)][2(L+1)] moments of the zero-inflow cell solution
     //   PhiinfT[N][2(L+1)]      moments of the response to [a_j; b_{j+1}]
     dvec EsrcT, PhisrcT, PhiinfT;
+    FPTree tree;
 };
+
+// false: use the eliminations (better there, a singular pair, or no cut fits).
+// maps: the cell maps of the types (FPFactors::EsrcT, PhisrcT, PhiinfT).
+bool build_fp_tree(int K, int N, int L, int slabs, const FPCellTypes &ct, const FPFactors &maps, FPTree &out);
 
 // sigma_s is [K][L+1] for this slab; sigma_a = sigma_t - sigma_s0,
 // sigma_tr = sigma_s0 - sigma_s1.  Returns false if a cell block is
 // singular.  The FPSA residual's scattering matrix is folded into the
-// source maps (EsrcT, PhisrcT act on phi_half - phi_old).
+// source maps (EsrcT, PhisrcT act on phi_half - phi_old).  With
+// tree_slabs > 0 (slabs solved together), a slab gets its doubling tree and the
+// cell maps instead of the eliminations' matrices (tree.stages is empty otherwise).
 bool build_fp_factors(int K, int N, int L, const double *h, const double *sigma_t,
                       const double *sigma_s, const dvec &mu, const dvec &w,
-                      const dvec &A, FPFactors &out, int chunk_hint = 0);
+                      const dvec &A, FPFactors &out, int chunk_hint = 0,
+                      int tree_slabs = 0);
 
 // The same from the removal coefficients of F directly: sigma_a, sigma_tr
 // [K].  sigma_s (nullable) as above; null leaves the scattering out of the
@@ -93,6 +174,7 @@ bool build_fp_factors(int K, int N, int L, const double *h, const double *sigma_
 // caller, and cell types depend on (h, sigma_a, sigma_tr) only.
 bool build_fp_factors_coef(int K, int N, int L, const double *h, const double *sigma_a,
                            const double *sigma_tr, const double *sigma_s, const dvec &mu,
-                           const dvec &w, const dvec &A, FPFactors &out, int chunk_hint = 0);
+                           const dvec &w, const dvec &A, FPFactors &out, int chunk_hint = 0,
+                           int tree_slabs = 0);
 
 }  // namespace snfpsa

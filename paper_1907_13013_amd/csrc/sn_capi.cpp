@@ -26,6 +26,7 @@
 using namespace snfpsa;
 
 static_assert(FP_CELLMATS == FP_CELL_MATS, "host and device factor layouts differ");
+static_assert(kFptWaves == kTreeWaves && kFptHdr == kTreeHdr && kFptMaxUnits == kTreeMaxUnits, "tree record sizes differ");
 static_assert(SN_KERNEL_COUNT == KID_COUNT, "kernel ids of the header and the kernels differ");
 
 namespace {
@@ -109,6 +110,10 @@ struct Slab {
     double *EsrcT = nullptr, *PhisrcT = nullptr, *PhiinfT = nullptr;
     std::vector<int32_t> seg_begin, seg_type;
     int chunk = 0, nchunks = 0;
+    // doubling tree (no stages: the eliminations above)
+    std::vector<FPTreeStage> tstages;
+    double *tfrag = nullptr;
+    int *trecs = nullptr;
     // source maps without the cell's sigma_s (shared factorisations): the
     // correction GEMMs scale phi_half - phi_old by sigma_s2 = [K][2][L+1]
     bool fold_ss = true;
@@ -234,18 +239,20 @@ enum {
     PH_FP_CARRY,
     PH_FP_FIXUP,
     PH_FP_UPDATE,     // FPSA: corrected moments per segment
-    PH_STOP,          // FPSA with several segments: the stopping test
+    PH_TREE,          // FPSA by doubling trees: the positions of TreeLaunch
+    PH_STOP = PH_TREE + 2 * kTreeMaxStages - 1,  // FPSA with several segments: the stopping test
     PH_COUNT
 };
 
 struct PlanItem {
     LaunchShape sh;
-    int kind = 0;  // 0 GEMM, 1 sweep, 2 Fokker-Planck, 3 stopping test, 4 grouped Fokker-Planck
+    int kind = 0;  // 0 GEMM, 1 sweep, 2 Fokker-Planck, 3 stopping test, 4 grouped Fokker-Planck, 5 tree
     GemmArgs g;
     SweepArgs sw;
     FPArgs f;
     StopArgs st;
     FPGroupArgs fg;
+    FPTreeArgs t;
     size_t vec_off = 0;  // kind 4: the group's FPSlabVecs in the plan's vector table
     IterPatch p;
     uintptr_t order = 0;  // items of one launch are ordered by this key
@@ -524,11 +531,67 @@ GemmArgs fp_update_args(const Workspace &W, const Slab &b, const double *phi_hal
     return g;
 }
 
+// The kernels of a slab's correction by its doubling tree: (kernel, position
+// of the launch in the slab's sequence, arguments).  Position i ascends stage
+// i, the root is at kTreeMaxStages - 1, and the descents mirror the ascents.
+struct TreeLaunch {
+    int kernel, pos;
+    FPTreeArgs a;
+};
+constexpr int kTreePositions = 2 * kTreeMaxStages - 1;
+
+std::vector<TreeLaunch> tree_launches(const Workspace &W, const Slab &b, const double *phi_half, const double *phi_old,
+                                      double *phi_new, SkipTest skip, const FusedStop *fs) {
+    const int S = (int)b.tstages.size();
+    std::vector<FPTreeArgs> st(S);
+    double *y = W.s, *later = W.fvec;  // cells' interfaces, then the later stages'
+    for (int i = 0; i < S; ++i) {
+        const FPTreeStage &t = b.tstages[i];
+        FPTreeArgs &a = st[i];
+        a.N = b.N; a.L2 = 2 * b.L1;
+        a.n = t.n; a.c = t.c; a.chunks = t.chunks; a.levels = t.levels;
+        a.rows = std::min(t.c, t.n);
+        a.nb = fp_tree_nb(a.N);
+        a.lda = (int)fp_tree_ld(a.N, a.L2); a.ldy = (int)fp_tree_ld(a.N, a.N);
+        a.rcpN = (unsigned)((((uint64_t)1 << 32) + a.N - 1) / a.N);
+        a.rcpL2 = (unsigned)((((uint64_t)1 << 32) + a.L2 - 1) / a.L2);
+        a.frag = b.tfrag; a.recs = b.trecs + t.rec0; a.rec_stride = t.rec_stride;
+        a.Yin = y;
+        a.Yout = later;
+        y = later;
+        later += (size_t)(t.chunks + 1) * b.N;
+        a.skip = skip;
+        a.exit_b0 = W.bvec;
+        a.exit_aK = W.pvec + (size_t)b.K * b.NH;
+        a.half = phi_half; a.old = phi_old; a.out = phi_new;
+        a.sigma = b.fold_ss ? nullptr : b.sigma_s2;
+        a.stop_slot = fs ? fs->slot : nullptr;
+    }
+    std::vector<TreeLaunch> out;
+    const int last = kTreePositions - 1;
+    if (S == 1) {
+        out.push_back({FPT_K_ALL, last, st[0]});
+        return out;
+    }
+    for (int i = 0; i + 1 < S; ++i) out.push_back({i == 0 ? FPT_K_LEAF_UP : FPT_K_UP, i, st[i]});
+    out.push_back({FPT_K_ROOT, kTreeMaxStages - 1, st[S - 1]});
+    for (int i = S - 2; i >= 0; --i) out.push_back({i == 0 ? FPT_K_UPDATE : FPT_K_DOWN, last - i, st[i]});
+    return out;
+}
+
+// whether a slab's correction carries the stopping test itself
+bool correct_stops(const Slab &b) { return !b.tstages.empty() || b.seg_begin.size() == 2; }
+
 void correct(sn_handle H, const Workspace &W, const Slab &b, const double *phi_half, const double *phi_old,
              double *phi_new, hipStream_t st, SkipTest skip = SkipTest(),
              const FusedStop *fs = nullptr, bool timed = true) {
     KernelTimer *const tm = timed ? H->timer : nullptr;
     const int L2 = 2 * b.L1;
+    if (!b.tstages.empty()) {
+        for (const TreeLaunch &t : tree_launches(W, b, phi_half, phi_old, phi_new, skip, fs))
+            launch_fpt(t.a, t.kernel, st, tm);
+        return;
+    }
     FPArgs f = fp_args(W, b, skip);
     if (b.seg_begin.size() == 2 && fp_fusable(b.NH, L2)) {
         // one cell type: the source GEMM rides on the additive-term kernel
@@ -695,7 +758,7 @@ static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool pro
         std::map<std::tuple<const double *, const double *, int, int, int>, std::vector<int>> by_key;
         for (int bi = 0; bi < ns; ++bi) {
             const Slab &b = h->slabs[bi];
-            if (b.NH > 64) continue;
+            if (b.NH > 64 || !b.tstages.empty()) continue;
             by_key[std::make_tuple((const double *)b.cellmats, (const double *)b.psi_fwd, b.K, b.NH, b.chunk)]
                 .push_back(bi);
         }
@@ -791,6 +854,22 @@ static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool pro
             add(PH_MOMENTS, it);
         }
         if (method != SN_FPSA) continue;
+        if (!b.tstages.empty()) {
+            FusedStop fs;
+            fs.ref = cur;
+            fs.slot = slot;
+            for (const TreeLaunch &tl : tree_launches(W, b, W.phi_half, cur, nxt, SkipTest(), &fs)) {
+                PlanItem it;
+                it.kind = 5;
+                it.t = tl.a;
+                it.sh = fpt_shape(tl.a, tl.kernel);
+                it.p = base;
+                it.p.flags |= PATCH_A1SUB_CUR | PATCH_C_NXT | PATCH_STOP;
+                it.order = (uintptr_t)b.tfrag;  // slabs sharing matrices side by side
+                add(PH_TREE + tl.pos, it);
+            }
+            continue;
+        }
         const bool single = b.seg_begin.size() == 2;
         for (size_t sg = 0; sg + 1 < b.seg_begin.size(); ++sg) {
             PlanItem it;
@@ -908,6 +987,7 @@ static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool pro
                 case 1: plan_group(kv.second, &PlanItem::sw, blob, where, plan.launches); break;
                 case 2: plan_group(kv.second, &PlanItem::f, blob, where, plan.launches); break;
                 case 4: plan_group(kv.second, &PlanItem::fg, blob, where, plan.launches); break;
+                case 5: plan_group(kv.second, &PlanItem::t, blob, where, plan.launches); break;
                 default: plan_group(kv.second, &PlanItem::st, blob, where, plan.launches); break;
             }
         }
@@ -1247,7 +1327,7 @@ sn_status sn_setup(const sn_problem_desc *d, void *stream, sn_handle *out) {
                     const dvec A = (d->fp_scheme == SN_FP_WFD) ? wfd_laplacian(N, mu, w) : mpd_laplacian(N, mu, w);
                     const dvec sa(K, key[3]), str(K, key[4]);
                     if (!build_fp_factors_coef(K, N, L, d->h + jobs[jb].second, sa.data(), str.data(), nullptr, mu, w,
-                                               A, mean_factors.at(key)))
+                                               A, mean_factors.at(key), 0, d->num_slabs))
                         failed.store(1);
                 }
             };
@@ -1294,6 +1374,7 @@ sn_status sn_setup(const sn_problem_desc *d, void *stream, sn_handle *out) {
             b.psi_right = d->psi_right ? H->upload(dvec(d->psi_right + half, d->psi_right + half + b.NH), st) : nullptr;
             if (H->has_fp) {
                 const bool mean = d->fp_coefficients == SN_FP_MEAN;
+                bool shared = false;
                 if (mean) {
                     auto it = fp_cache.find(mean_key[bi]);
                     if (it != fp_cache.end()) {
@@ -1303,7 +1384,9 @@ sn_status sn_setup(const sn_problem_desc *d, void *stream, sn_handle *out) {
                         b.EsrcT = o.EsrcT; b.PhisrcT = o.PhisrcT; b.PhiinfT = o.PhiinfT;
                         b.seg_begin = o.seg_begin; b.seg_type = o.seg_type;
                         b.chunk = o.chunk; b.nchunks = o.nchunks;
+                        b.tstages = o.tstages; b.tfrag = o.tfrag; b.trecs = o.trecs;
                         b.fold_ss = false;
+                        shared = true;
                     }
                     dvec s2((size_t)b.K * 2 * b.L1);
                     for (int j = 0; j < b.K; ++j)
@@ -1312,7 +1395,7 @@ sn_status sn_setup(const sn_problem_desc *d, void *stream, sn_handle *out) {
                                 s2[((size_t)j * 2 + nu) * b.L1 + l] = d->sigma_s[so + (int64_t)j * b.L1 + l];
                     b.sigma_s2 = H->upload(s2, st);
                 }
-                if (!mean || !b.cellmats) {
+                if (!shared) {
                     // Fokker-Planck factorisation (FP64, host): per-cell
                     // coefficients are factored for a group of slabs at a
                     // time on host threads, so that only one group's host
@@ -1338,7 +1421,8 @@ sn_status sn_setup(const sn_problem_desc *d, void *stream, sn_handle *out) {
                                     const dvec A = (d->fp_scheme == SN_FP_WFD) ? wfd_laplacian(N, m2, w2)
                                                                                : mpd_laplacian(N, m2, w2);
                                     if (!build_fp_factors(d->K[k], N, d->L[k], d->h + cc[k - bi], d->sigma_t + cc[k - bi],
-                                                          d->sigma_s + ss[k - bi], m2, w2, A, group_factors[k - bi]))
+                                                          d->sigma_s + ss[k - bi], m2, w2, A, group_factors[k - bi], 0,
+                                                          d->num_slabs))
                                         failed.store(k);
                                 }
                             };
@@ -1360,7 +1444,12 @@ sn_status sn_setup(const sn_problem_desc *d, void *stream, sn_handle *out) {
                     FPFactors &F = mean ? mean_factors.at(mean_key[bi]) : Fc;
                     b.fold_ss = F.folded_sigma_s;
                     if (mean) fp_cache.emplace(mean_key[bi], bi);
-                    {
+                    if (!F.tree.stages.empty()) {
+                        b.tstages = F.tree.stages;
+                        b.tstages = F.tree.stages;
+                        b.tfrag = H->upload(F.tree.frag, st);
+                        b.trecs = H->upload(F.tree.records, st);
+                    } else {
                         // device layout: all six matrices transposed, so that the
                         // threads of one cell (one per row) read consecutive addresses
                         // and a chain step's matrix copies verbatim into LDS
@@ -1375,10 +1464,7 @@ sn_status sn_setup(const sn_problem_desc *d, void *stream, sn_handle *out) {
                                         dst[(size_t)cc * b.NH + r] = src[(size_t)r * b.NH + cc];
                             }
                         b.cellmats = H->upload(dev, st);
-                    }
-                    {
                         // prefix and transfer products, transposed per matrix
-                        const size_t M2 = (size_t)b.NH * b.NH;
                         auto transposed = [&](const dvec &src) {
                             dvec dst(src.size());
                             for (size_t m = 0; m < src.size() / std::max<size_t>(M2, 1); ++m)
@@ -1392,9 +1478,11 @@ sn_status sn_setup(const sn_problem_desc *d, void *stream, sn_handle *out) {
                         b.theta_fwd = H->upload(transposed(F.theta_fwd), st);
                         b.theta_bwd = H->upload(transposed(F.theta_bwd), st);
                     }
-                    b.EsrcT = H->upload(F.EsrcT, st);
-                    b.PhisrcT = H->upload(F.PhisrcT, st);
-                    b.PhiinfT = H->upload(F.PhiinfT, st);
+                    if (F.tree.stages.empty()) {
+                        b.EsrcT = H->upload(F.EsrcT, st);
+                        b.PhisrcT = H->upload(F.PhisrcT, st);
+                        b.PhiinfT = H->upload(F.PhiinfT, st);
+                    }
                     b.seg_begin = F.seg_begin;
                     b.seg_type = F.seg_type;
                     b.chunk = F.chunk;
@@ -1944,7 +2032,7 @@ static sn_status solve_impl(sn_handle h, int32_t method, double tol, int32_t max
                     launch_sweep(a, false, sg, h->timer);
                     if (method == SN_FPSA) {
                         correct(h, W, b, W.phi_half, cur, nxt, sg, sk, &fs);
-                        if (b.seg_begin.size() != 2)
+                        if (!correct_stops(b))
                             launch_stopping_test(nxt, cur, nphi, fs.slot, sk, sg, h->timer);
                     }
                     continue;
@@ -1955,7 +2043,7 @@ static sn_status solve_impl(sn_handle h, int32_t method, double tol, int32_t max
                 if (method == SN_FPSA) {
                     moments(b, W.psi, W.phi_half, sg, h->timer, sk);
                     correct(h, W, b, W.phi_half, cur, nxt, sg, sk, &fs);
-                    if (b.seg_begin.size() != 2)
+                    if (!correct_stops(b))
                         launch_stopping_test(nxt, cur, nphi, fs.slot, sk, sg, h->timer);
                 } else {
                     moments(b, W.psi, nxt, sg, h->timer, sk, &fs);

@@ -109,6 +109,32 @@ struct FPArgs {
     const double *src_E = nullptr;                  // [L2][N]
 };
 
+// One stage of a slab's doubling tree (see FPTree in setup_math.hpp).
+constexpr int kFptWaves = 8, kFptHdr = 20, kFptMaxUnits = 128;
+struct FPTreeArgs {
+    int N = 0, L2 = 0;
+    int n = 0, c = 0, chunks = 0, levels = 0;   // the stage: leaves, leaves per chunk, chunks, levels
+    int rows = 0, lda = 0, ldy = 0;             // LDS: leaves of the largest chunk, row strides
+    unsigned rcpN = 0, rcpL2 = 0;               // ceil(2^32 / N), ceil(2^32 / L2): row of a staged element
+    // right operands [K][cols] in fragment order: per column tile of 16 and
+    // pair of k-steps of 4, lane l's values of rows 8 p + l / 16 and
+    // 8 p + 4 + l / 16, column 16 c + l % 16; K padded with zero rows to a
+    // multiple of 4 nb, columns to one of 16
+    int nb = 0;                                 // k-steps per batch of operands
+    const double *frag = nullptr;
+    const int *recs = nullptr;                  // per chunk and wave (FPTree::records)
+    int rec_stride = 0;
+    double *Yin = nullptr;                      // [n + 1][N] the stage's interfaces (cells: rows 1 .. n - 1)
+    double *Yout = nullptr;                     // [chunks + 1][N] the next stage's
+    // leaf stage: moments, result
+    const double *half = nullptr, *old = nullptr;   // [n][L2]
+    const double *sigma = nullptr;                  // [n][L2] or null (folded into the maps)
+    double *out = nullptr;
+    unsigned long long *stop_slot = nullptr;        // max |out - old| folded in, or null
+    double *exit_b0 = nullptr, *exit_aK = nullptr;  // [N/2] the slab's outgoing fluxes (root)
+    SkipTest skip;
+};
+
 // Whether launch_fp_recurrences can form the Fokker-Planck source inside its
 // additive-term kernel for a slab of NH = N/2 and L2 = 2 (L + 1).
 bool fp_fusable(int NH, int L2);
@@ -243,8 +269,12 @@ enum MultiKernel {
     MK_GFP_MATVEC,    // grouped forms (FPGroupArgs entries), v1 = NHP <= 64
     MK_GFP_CHAIN,
     MK_GFP_CARRY,
-    MK_GFP_FIXUP
+    MK_GFP_FIXUP,
+    MK_FPT            // doubling tree: v1 products per batch, v2 the kernel (FptKernel)
 };
+// the tree's kernels: ascent from the cells, ascent of a later stage, the
+// root chunk, descent, descent with the update, and all of it in one chunk
+enum FptKernel { FPT_K_LEAF_UP = 0, FPT_K_UP, FPT_K_ROOT, FPT_K_DOWN, FPT_K_UPDATE, FPT_K_ALL };
 struct LaunchShape {
     int kernel = 0, v1 = 0, v2 = 0;
     int gx = 1, gy = 1;
@@ -272,6 +302,9 @@ struct MultiLaunch {
     int nblocks = 0;
     unsigned lds = 0;
 };
+LaunchShape fpt_shape(const FPTreeArgs &f, int kernel);
+void launch_fpt(const FPTreeArgs &f, int kernel, hipStream_t s, KernelTimer *t);
+void launch_fpt_multi(const MultiLaunch &L, const int *iter, hipStream_t s, KernelTimer *t);
 void launch_multi(const MultiLaunch &L, const int *iter, hipStream_t s, KernelTimer *t);
 // iter[0] += 1 (the end of one batched iteration)
 void launch_iter_step(int *iter, hipStream_t s);
