@@ -737,6 +737,12 @@ static void plan_group(const std::vector<const PlanItem *> &items, const A PlanI
     out.push_back(L);
 }
 
+// A slab of a batched solve stops iterating once its test value is at most
+// this share of tol.  Its iterations until the slowest slab passes tol used
+// to run in full (a share of 0); the share keeps most of the digits that
+// they added beyond tol.
+constexpr double kBatchGate = 1.0 / 64;
+
 static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool problem_bc, double tol,
                           F64Plan **out) {
     F64Batch &B = *h->f64b;
@@ -749,6 +755,8 @@ static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool pro
         }
     }
     const int ns = (int)h->slabs.size();
+    SkipTest gate;  // prev is the iteration's (PATCH_SKIP)
+    gate.tol = tol * kBatchGate;
     // slabs sharing one factorisation (same factor arrays and sizes; padded
     // half-width <= 64) run their recurrences as groups of at most
     // kFPGroupMax slabs
@@ -801,7 +809,7 @@ static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool pro
         if (!fuse) {
             PlanItem it;
             it.kind = 0;
-            it.g = scatter_args(b, cur, qe, W.q);
+            it.g = scatter_args(b, cur, qe, W.q, gate);
             it.sh = gemm_shape(it.g);
             it.p = base;
             it.p.flags |= PATCH_A1_CUR;
@@ -809,7 +817,7 @@ static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool pro
             add(PH_SCATTER, it);
         }
         {
-            SweepArgs a = sweep_args(W, b, W.q, W.psi, problem_bc);
+            SweepArgs a = sweep_args(W, b, W.q, W.psi, problem_bc, gate);
             PlanItem it;
             it.kind = 1;
             it.p = base;
@@ -841,12 +849,12 @@ static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool pro
             it.kind = 0;
             it.p = base;
             if (method == SN_FPSA) {
-                it.g = moments_args(b, W.psi, W.phi_half);
+                it.g = moments_args(b, W.psi, W.phi_half, gate);
             } else {
                 FusedStop fs;
                 fs.ref = cur;
                 fs.slot = slot;
-                it.g = moments_args(b, W.psi, nxt, SkipTest(), &fs);
+                it.g = moments_args(b, W.psi, nxt, gate, &fs);
                 it.p.flags |= PATCH_C_NXT | PATCH_STOP;
             }
             it.sh = gemm_shape(it.g);
@@ -858,7 +866,7 @@ static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool pro
             FusedStop fs;
             fs.ref = cur;
             fs.slot = slot;
-            for (const TreeLaunch &tl : tree_launches(W, b, W.phi_half, cur, nxt, SkipTest(), &fs)) {
+            for (const TreeLaunch &tl : tree_launches(W, b, W.phi_half, cur, nxt, gate, &fs)) {
                 PlanItem it;
                 it.kind = 5;
                 it.t = tl.a;
@@ -874,7 +882,7 @@ static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool pro
         for (size_t sg = 0; sg + 1 < b.seg_begin.size(); ++sg) {
             PlanItem it;
             it.kind = 0;
-            it.g = fp_source_args(W, b, W.phi_half, cur, sg, SkipTest());
+            it.g = fp_source_args(W, b, W.phi_half, cur, sg, gate);
             it.sh = gemm_shape(it.g);
             it.p = base;
             it.p.flags |= PATCH_A1SUB_CUR;
@@ -885,7 +893,7 @@ static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool pro
         if (group_of[bi] < 0) {
             PlanItem it;
             it.kind = 2;
-            it.f = fp_args(W, b, SkipTest());
+            it.f = fp_args(W, b, gate);
             it.p = base;
             it.order = (uintptr_t)b.cellmats;  // slabs sharing factors side by side
             LaunchShape sh[4];
@@ -900,10 +908,10 @@ static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool pro
             const std::vector<int> &grp = groups[group_of[bi]];
             PlanItem it;
             it.kind = 4;
-            it.fg.f = fp_args(W, b, SkipTest());
+            it.fg.f = fp_args(W, b, gate);
             it.fg.nslab = (int)grp.size();
             it.fg.hist_stride = ns;
-            it.fg.tol = tol;
+            it.fg.tol = gate.tol;
             it.vec_off = vecs.size();
             for (int sb : grp) {
                 const Workspace &V = B.ws[sb];
@@ -930,7 +938,7 @@ static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool pro
             fs.slot = slot;
             PlanItem it;
             it.kind = 0;
-            it.g = fp_update_args(W, b, W.phi_half, cur, nxt, sg, SkipTest(), &fs);
+            it.g = fp_update_args(W, b, W.phi_half, cur, nxt, sg, gate, &fs);
             it.sh = gemm_shape(it.g);
             it.p = base;
             it.p.flags |= PATCH_A1SUB_CUR | PATCH_C_NXT | (single ? PATCH_STOP : 0u);
@@ -945,6 +953,7 @@ static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool pro
             it.st.b = cur;
             it.st.n = nphi;
             it.st.slot = slot;
+            it.st.skip = gate;
             it.sh = stop_shape(nphi);
             it.p = base;
             it.p.flags |= PATCH_STOPTEST;
@@ -1029,8 +1038,11 @@ static sn_status solve_batched_f64(sn_handle h, int32_t method, double tol, int3
     }
     sn_status ps = f64_plan(h, method, q_ext, problem_bc, tol, &plan);
     if (ps != SN_OK) return ps;
-    std::vector<int> its(ns, 0);
+    // its: iterations until the test passed; last: the slab's last executed
+    // iteration (0: none stopped it yet), whose iterate is the result
+    std::vector<int> its(ns, 0), last(ns, 0);
     std::vector<char> bad(ns, 0);
+    const double gate = tol * kBatchGate;
     try {
         HIPCHK(hipMemcpyAsync(B.phiA, phi, (size_t)h->phi_len * sizeof(double), hipMemcpyDeviceToDevice, st));
         static const int one = 1;
@@ -1089,22 +1101,35 @@ static sn_status solve_batched_f64(sn_handle h, int32_t method, double tol, int3
                                       (size_t)c * ns * sizeof(unsigned long long), hipMemcpyDeviceToHost, rs));
             });
             HIPCHK(hipStreamSynchronize(rs));
+            // iterations that the slowest slab needs to reach the gate, from
+            // its recent contraction rate
+            double need = 0.0;
             for (int b = 0; b < ns; ++b) {
-                if (its[b]) continue;
-                for (int i = 0; i < nb; ++i) {
+                auto value = [&](int m) {
                     double v;
-                    std::memcpy(&v, &h->hist_host[hist_row(launched + i + 1) * ns + b], sizeof(double));
-                    if (resid_hist) resid_hist[(size_t)b * max_iter + launched + i] = v;
-                    if (passes(v)) {
-                        its[b] = launched + i + 1;
-                        bad[b] = !std::isfinite(v);
-                        --remaining;
-                        break;
+                    std::memcpy(&v, &h->hist_host[hist_row(m) * ns + b], sizeof(double));
+                    return v;
+                };
+                for (int m = launched + 1; m <= launched + nb && !last[b]; ++m) {
+                    const double v = value(m);
+                    if (!its[b]) {
+                        if (resid_hist) resid_hist[(size_t)b * max_iter + m - 1] = v;
+                        if (passes(v)) {
+                            its[b] = m;
+                            bad[b] = !std::isfinite(v);
+                            --remaining;
+                        }
                     }
+                    if (v <= gate || !std::isfinite(v)) last[b] = m;
                 }
+                if (its[b]) continue;
+                const int m = launched + nb, d = std::min(nb - 1, 8);
+                const double v = value(m), rho = d > 0 ? std::pow(v / value(m - d), 1.0 / d) : 1.0;
+                need = std::max(need, rho > 0.0 && rho < 1.0 && gate > 0.0 ? std::log(gate / v) / std::log(rho) + 1.0
+                                                                            : (double)kHistBatch);
             }
             launched += nb;
-            batch = std::min(2 * batch, kHistBatch);
+            batch = (int)std::min(std::ceil(need), (double)std::min(2 * batch, kHistBatch));
         }
         if (rs != st) {
             HIPCHK(hipEventRecord(B.gev, rs));
@@ -1119,7 +1144,7 @@ static sn_status solve_batched_f64(sn_handle h, int32_t method, double tol, int3
                 result = SN_NOT_CONVERGED;
             }
             iters[b] = its[b];
-            const double *fin = (its[b] & 1) ? W.phiB : W.phiA;
+            const double *fin = ((last[b] ? last[b] : launched) & 1) ? W.phiB : W.phiA;
             HIPCHK(hipMemcpyAsync(phi + sl.phi_off, fin, (size_t)sl.K * 2 * sl.L1 * sizeof(double),
                                   hipMemcpyDeviceToDevice, st));
             if (psi_exit)
