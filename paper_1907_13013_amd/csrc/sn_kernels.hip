@@ -497,37 +497,40 @@ void launch_gemm(const GemmArgs &g, hipStream_t s, KernelTimer *t) {
 // ---------------------------------------------------------------------------
 constexpr int SWEEP_INKERNEL_TILES = 128;
 
+// The cell's two maps of its inflow x: outflow a x + b, inflow-side node
+// p x + r.  Needs no inflow, so it is formed before the block waits for one.
 struct CellCoef {
-    double a, b, gin, gout, tau, den_inv;
+    double a, b, p, r;
 };
 
 __device__ __forceinline__ CellCoef cell_coef(double inv_absmu, double hj, double stj,
                                               double yin, double yout, bool adjoint) {
-    CellCoef c;
-    c.tau = stj * hj * inv_absmu;
-    c.den_inv = 1.0 / (6.0 + c.tau * (4.0 + c.tau));
-    if (adjoint) {
-        c.gin = yin;
-        c.gout = yout;
-    } else {
+    const double tau = stj * hj * inv_absmu;
+    const double di = 1.0 / (6.0 + tau * (4.0 + tau));
+    double gin = yin, gout = yout;
+    if (!adjoint) {
         const double f = hj * inv_absmu * (1.0 / 6.0);
-        c.gin = f * (2.0 * yin + yout);
-        c.gout = f * (yin + 2.0 * yout);
+        gin = f * (2.0 * yin + yout);
+        gout = f * (yin + 2.0 * yout);
     }
-    c.a = (6.0 - 2.0 * c.tau) * c.den_inv;
-    c.b = ((6.0 + 4.0 * c.tau) * c.gout + (6.0 - 2.0 * c.tau) * c.gin) * c.den_inv;
+    CellCoef c;
+    c.a = (6.0 - 2.0 * tau) * di;
+    c.b = ((6.0 + 4.0 * tau) * gout + (6.0 - 2.0 * tau) * gin) * di;
+    c.p = (6.0 + 4.0 * tau) * di;
+    c.r = ((6.0 + 4.0 * tau) * gin - (6.0 + 2.0 * tau) * gout) * di;
     return c;
 }
 
 // Direction of the recurrence for angle n: +1 left-to-right, -1 right-to-left.
-__device__ __forceinline__ int sweep_dir(double mu, bool adjoint) {
-    return ((mu > 0.0) != adjoint) ? 1 : -1;
+// The angles ascend, so the upper half has mu > 0; taking the direction from
+// the index keeps the loads that depend on it from waiting for mu.
+__device__ __forceinline__ int sweep_dir(const SweepArgs &s, int n, bool adjoint) {
+    return ((2 * n >= s.N) != adjoint) ? 1 : -1;
 }
 
 __device__ __forceinline__ double boundary_inflow(const SweepArgs &s, int n, bool adjoint) {
     if (adjoint) return 0.0;
-    const double mu = s.mu[n];
-    if (mu > 0.0) return s.psi_left ? s.psi_left[n - s.N / 2] : 0.0;
+    if (2 * n >= s.N) return s.psi_left ? s.psi_left[n - s.N / 2] : 0.0;
     return s.psi_right ? s.psi_right[n] : 0.0;
 }
 
@@ -607,23 +610,26 @@ __device__ __forceinline__ void tile_gemm(const double *A, int R, const double *
     tile_scatter<NP>(R, nc, acc, pv, out);
 }
 
-// Copies a rows x NP block into LDS at row stride NP + 1 with element
-// (r, c) = get(r, c) for c < cols and 0 for cols <= c < NP (rows <= 64, so
-// at most 16 elements per thread).  Load indices past the block are clamped,
-// so the loads carry no branches and all are issued before the first store.
+// Copies a rows x NP block into LDS at row stride NP + 1 (rows <= 64, so at
+// most 16 elements per thread): stage_load issues the loads get(r, c) at
+// indices clamped to the block, without branches, stage_store puts the
+// values, 0 where r >= rows_in or c >= cols.  Other loads and work go between.
 template <int NP, class Get>
-__device__ __forceinline__ void stage_block(double *dst, int rows, int cols, Get &&get) {
+__device__ __forceinline__ void stage_load(double (&v)[16], int rows, int cols, Get &&get) {
     const int n = rows * NP, t = threadIdx.x;
-    double v[16];
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
         const int idx = min(t + 256 * u, n - 1);
         v[u] = get(idx / NP, min(idx % NP, cols - 1));
     }
+}
+template <int NP>
+__device__ __forceinline__ void stage_store(double *dst, const double (&v)[16], int rows, int rows_in, int cols) {
+    const int n = rows * NP, t = threadIdx.x;
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
         const int idx = t + 256 * u;
-        if (idx < n) dst[(idx / NP) * (NP + 1) + idx % NP] = (idx % NP) < cols ? v[u] : 0.0;
+        if (idx < n) dst[(idx / NP) * (NP + 1) + idx % NP] = (idx % NP) < cols && idx / NP < rows_in ? v[u] : 0.0;
     }
 }
 
@@ -649,9 +655,14 @@ static size_t fused_apply_lds(const SweepArgs &s, int NP) {
 constexpr int SWEEP_BATCH = 8;
 
 // NP > 0: fused source (q of the tile from phi by MFMA, see SweepArgs).
+//
+// A tile is a chain of latencies, so the loads of every stage go out before
+// the convergence gate is resolved and the first stage waits (wide tiles
+// hold back the last ones for registers: three blocks a CU).  K = 1500,
+// N = 16: 8.2 us with each stage loading for itself, 7.1 now; 32 slabs of
+// 2048 cells, N = 64: 82 and 77.
 template <int NP>
 __device__ __forceinline__ void sweep_aggregate_body(SweepArgs s, bool adjoint, const int bx_, const int by_) {
-    if (skipped(s.skip)) return;
     extern __shared__ double dyn[];
     __shared__ double shA[256], shB[256];
     const int N = s.N, S = s.S;
@@ -659,8 +670,38 @@ __device__ __forceinline__ void sweep_aggregate_body(SweepArgs s, bool adjoint, 
     const int tile = bx_;
     const int c0 = tile * s.TC, c1 = min(s.K, c0 + s.TC);
     constexpr bool fused = NP > 0;
+    constexpr bool wide = NP == 64;  // fewer loads ahead, so that three blocks' registers fit a CU
     constexpr int ldq = NP + 1;
     double *qt = dyn;  // fused: the tile's source [2 TC][NP+1], over the A operand
+    const bool live = sc < S;
+    const double inv = s.inv_absmu[n];
+    const int dir = sweep_dir(s, n, adjoint);
+    const int j0 = c0 + sc * s.sub, j1 = min(c1, c0 + (sc + 1) * s.sub);
+    const int in_node = dir > 0 ? 0 : 1;
+    const int len = live ? j1 - j0 : 0;
+    double yin[SWEEP_BATCH], yout[SWEEP_BATCH], hh[SWEEP_BATCH], st[SWEEP_BATCH];
+    auto cell = [&](int i) { return min(dir > 0 ? j0 + min(i, max(len - 1, 0)) : j1 - 1 - min(i, max(len - 1, 0)), s.K - 1); };
+    auto load_cells = [&](int i0) {
+#pragma unroll
+        for (int u = 0; u < SWEEP_BATCH; ++u) {
+            hh[u] = s.h[cell(i0 + u)];
+            st[u] = s.sigma_t[cell(i0 + u)];
+        }
+    };
+    auto load_source = [&](int i0) {
+#pragma unroll
+        for (int u = 0; u < SWEEP_BATCH; ++u) {
+            const int j = cell(i0 + u);
+            if constexpr (fused) {
+                yin[u] = qt[((j - c0) * 2 + in_node) * ldq + n];
+                yout[u] = qt[((j - c0) * 2 + (1 - in_node)) * ldq + n];
+            } else {
+                yin[u] = s.q[((size_t)j * 2 + in_node) * N + n];
+                yout[u] = s.q[((size_t)j * 2 + (1 - in_node)) * N + n];
+            }
+        }
+    };
+    if constexpr (!wide) load_cells(0);
     if constexpr (fused) {
         // q = (phi .* sigma_s) x Mt + q_ext for the tile's R node rows
         const int L1 = s.L1, R = 2 * (c1 - c0);
@@ -668,16 +709,21 @@ __device__ __forceinline__ void sweep_aggregate_body(SweepArgs s, bool adjoint, 
         double *Bt = At + (size_t)2 * s.TC * ldq;
         const bool has = s.src_qext != nullptr;
         const double *qe = has ? s.src_qext : s.q_out;  // a valid address either way
-        double pv[4][4];
+        double pv[4][4], va[16], vs[16], vb[16];
+        auto load_b = [&]() { stage_load<NP>(vb, NP, N, [&](int r, int c) { return s.src_Mt[(size_t)min(r, L1 - 1) * N + c]; }); };
+        stage_load<NP>(va, R, L1, [&](int r, int l) { return s.src_phi[((size_t)c0 * 2 + r) * L1 + l]; });
+        stage_load<NP>(vs, R, L1, [&](int r, int l) { return s.src_sigma_s[(size_t)(c0 + r / 2) * L1 + l]; });
+        if constexpr (!wide) load_b();
         tile_prefetch<NP>(R, N, pv, [&](int row, int col) { return qe[((size_t)c0 * 2 + row) * N + col]; });
-        stage_block<NP>(At, R, L1, [&](int r, int l) {
-            return s.src_phi[((size_t)c0 * 2 + r) * L1 + l] * s.src_sigma_s[(size_t)(c0 + r / 2) * L1 + l];
-        });
-        stage_block<NP>(Bt, NP, N, [&](int r, int c) { return s.src_Mt[(size_t)min(r, L1 - 1) * N + c]; });
-        __syncthreads();
-        // rows of Bt past L1 hold Mt's last row: zero them (A is zero there
-        // too, but 0 x finite is what keeps the padding exact)
-        for (int idx = t; idx < (NP - L1) * NP; idx += 256) Bt[(L1 + idx / NP) * ldq + idx % NP] = 0.0;
+        if (skipped(s.skip)) return;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) va[u] *= vs[u];
+        stage_store<NP>(At, va, R, R, L1);
+        if constexpr (wide) {
+            load_b();
+            load_cells(0);
+        }
+        stage_store<NP>(Bt, vb, NP, L1, N);
         __syncthreads();
         d4 acc[4];
         tile_products<NP>(At, R, Bt, acc);
@@ -688,30 +734,14 @@ __device__ __forceinline__ void sweep_aggregate_body(SweepArgs s, bool adjoint, 
             s.q_out[((size_t)c0 * 2 + row) * N + col] = v;
         });
         __syncthreads();
+    } else {
+        if (skipped(s.skip)) return;
     }
     double A = 1.0, B = 0.0;
-    if (sc < S) {
-        const double mu = s.mu[n], inv = s.inv_absmu[n];
-        const int dir = sweep_dir(mu, adjoint);
-        const int j0 = c0 + sc * s.sub, j1 = min(c1, c0 + (sc + 1) * s.sub);
-        const int in_node = dir > 0 ? 0 : 1;
-        const int len = j1 - j0;
+    if (live) {
         for (int i0 = 0; i0 < len; i0 += SWEEP_BATCH) {
-            double yin[SWEEP_BATCH], yout[SWEEP_BATCH], hh[SWEEP_BATCH], st[SWEEP_BATCH];
-#pragma unroll
-            for (int u = 0; u < SWEEP_BATCH; ++u) {
-                const int i = min(i0 + u, len - 1);
-                const int j = dir > 0 ? j0 + i : j1 - 1 - i;
-                if constexpr (fused) {
-                    yin[u] = qt[((j - c0) * 2 + in_node) * ldq + n];
-                    yout[u] = qt[((j - c0) * 2 + (1 - in_node)) * ldq + n];
-                } else {
-                    yin[u] = s.q[((size_t)j * 2 + in_node) * N + n];
-                    yout[u] = s.q[((size_t)j * 2 + (1 - in_node)) * N + n];
-                }
-                hh[u] = s.h[j];
-                st[u] = s.sigma_t[j];
-            }
+            if (i0 > 0) load_cells(i0);
+            load_source(i0);
 #pragma unroll
             for (int u = 0; u < SWEEP_BATCH; ++u) {
                 if (i0 + u < len) {
@@ -728,7 +758,6 @@ __device__ __forceinline__ void sweep_aggregate_body(SweepArgs s, bool adjoint, 
     shB[t] = B;
     __syncthreads();
     if (sc == 0) {
-        const int dir = sweep_dir(s.mu[n], adjoint);
         double TA = 1.0, TB = 0.0;
         for (int i = 0; i < S; ++i) {
             const int ss = dir > 0 ? i : S - 1 - i;
@@ -742,12 +771,12 @@ __device__ __forceinline__ void sweep_aggregate_body(SweepArgs s, bool adjoint, 
 }
 
 template <int NP>
-__global__ void __launch_bounds__(256) sweep_aggregate(SweepArgs s, bool adjoint) {
+__global__ void __launch_bounds__(256, 2) sweep_aggregate(SweepArgs s, bool adjoint) {
     sweep_aggregate_body<NP>(s, adjoint, (int)blockIdx.x, (int)blockIdx.y);
 }
 
 template <int NP>
-__global__ void __launch_bounds__(256) sweep_aggregate_multi(const MultiEntry<SweepArgs> *E, const BlockRef *br, const int *iter) {
+__global__ void __launch_bounds__(256, 2) sweep_aggregate_multi(const MultiEntry<SweepArgs> *E, const BlockRef *br, const int *iter) {
     const BlockRef r = br[blockIdx.x];
     const MultiEntry<SweepArgs> &e = E[r.entry];
     SweepArgs a = e.a;
@@ -774,7 +803,7 @@ __device__ __forceinline__ void sweep_scan_groups_body(SweepArgs s, bool adjoint
     const int N = s.N;
     const int n = bx_ * 64 + threadIdx.x;
     if (n >= N) return;
-    const int dir = sweep_dir(s.mu[n], adjoint);
+    const int dir = sweep_dir(s, n, adjoint);
     const int g = by_;
     const int i0 = g * SCAN_GROUP, i1 = min(s.ntiles, i0 + SCAN_GROUP);
     double A = 1.0, B = 0.0;
@@ -816,7 +845,7 @@ __device__ __forceinline__ void sweep_scan_carry_body(SweepArgs s, bool adjoint,
     const int N = s.N;
     const int n = bx_ * 64 + threadIdx.x;
     if (n >= N) return;
-    const int dir = sweep_dir(s.mu[n], adjoint);
+    const int dir = sweep_dir(s, n, adjoint);
     const int g = by_;
     const int i0 = g * SCAN_GROUP, i1 = min(s.ntiles, i0 + SCAN_GROUP);
     double x = boundary_inflow(s, n, adjoint);
@@ -867,11 +896,13 @@ __global__ void __launch_bounds__(64) sweep_scan_carry_multi(const MultiEntry<Sw
 // Every load that does not depend on the carry (the tile aggregates before
 // this tile, this tile's sub-chunk aggregates, the first batch of sweep
 // inputs, and in fused mode Vt and the stopping-test reference) is issued
-// at the start, so the block waits on memory about once before the sweep.
+// at the start, before the convergence gate is resolved, and the cells' maps
+// are formed while the block gathers the carry, so the block waits on memory
+// about once before the sweep.  K = 1500, N = 16: 10.0 us with the maps in
+// the recurrence and directions read from mu, 9.4 now.
 // NP > 0: fused moments (and stopping test) of the swept tile, see SweepArgs.
 template <int NP>
 __device__ __forceinline__ void sweep_apply_body(SweepArgs s, bool adjoint, bool inkernel_carry, const int bx_, const int by_) {
-    if (skipped(s.skip)) return;
     extern __shared__ double dyn[];
     __shared__ double shA[256], shB[256], subA[256], subB[256];
     const int N = s.N, S = s.S;
@@ -879,12 +910,30 @@ __device__ __forceinline__ void sweep_apply_body(SweepArgs s, bool adjoint, bool
     const bool live = sc < S;
     const int tile = bx_;
     const int c0 = tile * s.TC, c1 = min(s.K, c0 + s.TC);
-    const double mu = s.mu[n], inv = s.inv_absmu[n];
-    const int dir = sweep_dir(mu, adjoint);
+    const double inv = s.inv_absmu[n];
+    const int dir = sweep_dir(s, n, adjoint);
     constexpr bool fused = NP > 0;
     constexpr int ldp = NP + 1;
     double *pt = dyn;                                  // fused: swept tile [2 TC][NP+1]
     double *Vs = dyn + (size_t)2 * s.TC * ldp;         // fused: Vt [NP][NP+1]
+    // the maps of the tiles before this one in sweep order, split into S
+    // contiguous runs, folded in batches of 16
+    const int P = dir > 0 ? tile : s.ntiles - 1 - tile;
+    const int Q = (P + S - 1) / S;
+    const int p0 = sc * Q, p1 = live && inkernel_carry ? min(P, p0 + Q) : 0;
+    double ta[16], tb[16];
+    auto load_maps = [&](int i) {
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            const int ii = max(min(i + u, p1 - 1), 0);
+            const int tt = dir > 0 ? ii : s.ntiles - 1 - ii;
+            ta[u] = s.tileA[(size_t)tt * N + n];
+            tb[u] = s.tileB[(size_t)tt * N + n];
+        }
+    };
+    constexpr bool wide = NP == 64;  // fewer loads ahead: two blocks' registers fit a CU
+    if constexpr (!wide)
+        if (p0 < p1) load_maps(p0);
     // this tile's sub-chunk aggregates (S x N <= 256 values, one per thread)
     const double sa = live ? s.subA[((size_t)tile * S + sc) * N + n] : 1.0;
     const double sb = live ? s.subB[((size_t)tile * S + sc) * N + n] : 0.0;
@@ -911,45 +960,52 @@ __device__ __forceinline__ void sweep_apply_body(SweepArgs s, bool adjoint, bool
     const int L1 = s.L1, R = 2 * (c1 - c0);
     const bool stop = fused && s.mom_ref != nullptr;
     if constexpr (fused) {
-        stage_block<NP>(Vs, NP, L1, [&](int r, int c) { return s.mom_Vt[(size_t)min(r, N - 1) * L1 + c]; });
+        double vv[16];
+        stage_load<NP>(vv, NP, L1, [&](int r, int c) { return s.mom_Vt[(size_t)min(r, N - 1) * L1 + c]; });
         const double *ref = stop ? s.mom_ref : s.mom_out;  // a valid address either way
         tile_prefetch<NP>(R, L1, pv, [&](int row, int col) { return ref[((size_t)c0 * 2 + row) * L1 + col]; });
+        if (skipped(s.skip)) return;
+        stage_store<NP>(Vs, vv, NP, N, L1);
+        if constexpr (wide)
+            if (p0 < p1) load_maps(p0);
         for (int idx = t; idx < R * (NP - N); idx += 256)
             pt[(idx / (NP - N)) * ldp + N + idx % (NP - N)] = 0.0;
+    } else {
+        if (skipped(s.skip)) return;
     }
-    double x;
-    if (inkernel_carry) {
-        // tiles before this one in sweep order, split into S contiguous runs,
-        // folded in batches of 16
-        const int P = dir > 0 ? tile : s.ntiles - 1 - tile;
-        const int Q = (P + S - 1) / S;
-        double A = 1.0, B = 0.0;
-        if (live) {
-            const int i0 = sc * Q, i1 = min(P, i0 + Q);
-            for (int i = i0; i < i1; i += 16) {
-                double a[16], b[16];
+    double x = boundary_inflow(s, n, adjoint);
+    double A = 1.0, B = 0.0;
+    for (int i = p0; i < p1; i += 16) {
+        if (i > p0) load_maps(i);
 #pragma unroll
-                for (int u = 0; u < 16; ++u) {
-                    const int ii = min(i + u, i1 - 1);
-                    const int tt = dir > 0 ? ii : s.ntiles - 1 - ii;
-                    a[u] = s.tileA[(size_t)tt * N + n];
-                    b[u] = s.tileB[(size_t)tt * N + n];
-                }
-#pragma unroll
-                for (int u = 0; u < 16; ++u) {
-                    if (i + u < i1) {
-                        B = a[u] * B + b[u];
-                        A = a[u] * A;
-                    }
-                }
+        for (int u = 0; u < 16; ++u) {
+            if (i + u < p1) {
+                B = ta[u] * B + tb[u];
+                A = ta[u] * A;
             }
         }
-        shA[t] = A;
-        shB[t] = B;
-        subA[t] = sa;
-        subB[t] = sb;
-        __syncthreads();
-        x = boundary_inflow(s, n, adjoint);
+    }
+    shA[t] = A;
+    shB[t] = B;
+    subA[t] = sa;
+    subB[t] = sb;
+    // the first batch's maps, formed while the block gathers
+    double ca[SWEEP_BATCH], cb[SWEEP_BATCH], cp[SWEEP_BATCH], cr[SWEEP_BATCH];
+    auto maps = [&](int i0) {
+#pragma unroll
+        for (int u = 0; u < SWEEP_BATCH; ++u) {
+            if (i0 + u < len) {
+                const CellCoef c = cell_coef(inv, hh[u], st[u], yin[u], yout[u], adjoint);
+                ca[u] = c.a;
+                cb[u] = c.b;
+                cp[u] = c.p;
+                cr[u] = c.r;
+            }
+        }
+    };
+    maps(0);
+    __syncthreads();
+    if (inkernel_carry) {
         for (int i = 0; i < S; ++i) x = shA[i * N + n] * x + shB[i * N + n];
         if (live && sc == 0 && s.exit && P == s.ntiles - 1) {
             // last tile in sweep order: its outflow is the far-face exit flux
@@ -957,9 +1013,6 @@ __device__ __forceinline__ void sweep_apply_body(SweepArgs s, bool adjoint, bool
             s.exit[n] = TA * x + TB;
         }
     } else {
-        subA[t] = sa;
-        subB[t] = sb;
-        __syncthreads();
         x = s.carry[(size_t)tile * N + n];
     }
     if (live) {
@@ -969,17 +1022,18 @@ __device__ __forceinline__ void sweep_apply_body(SweepArgs s, bool adjoint, bool
             for (int i = S - 1; i > sc; --i) x = subA[i * N + n] * x + subB[i * N + n];
         }
         for (int i0 = 0; i0 < len; i0 += SWEEP_BATCH) {
-            if (i0 > 0) load_batch(i0);
+            if (i0 > 0) {
+                load_batch(i0);
+                maps(i0);
+            }
 #pragma unroll
             for (int u = 0; u < SWEEP_BATCH; ++u) {
                 if (i0 + u < len) {
                     const int j = dir > 0 ? j0 + i0 + u : j1 - 1 - i0 - u;
                     const size_t iin = ((size_t)j * 2 + in_node) * N + n;
                     const size_t iout = ((size_t)j * 2 + (1 - in_node)) * N + n;
-                    const CellCoef c = cell_coef(inv, hh[u], st[u], yin[u], yout[u], adjoint);
-                    const double vout = c.a * x + c.b;
-                    const double vin =
-                        ((6.0 + 4.0 * c.tau) * (c.gin + x) - (6.0 + 2.0 * c.tau) * c.gout) * c.den_inv;
+                    const double vout = ca[u] * x + cb[u];
+                    const double vin = cp[u] * x + cr[u];
                     if (adjoint) {
                         // x = (h/(6|mu|)) [[2,1],[1,2]] zeta  (node order in/out is symmetric)
                         const double f = hh[u] * inv * (1.0 / 6.0);
@@ -1001,9 +1055,7 @@ __device__ __forceinline__ void sweep_apply_body(SweepArgs s, bool adjoint, bool
         }
     }
     if constexpr (fused) {
-        // moments of the tile (and the stopping test) on the swept values;
-        // rows of Vs past N hold Vt's last row: zero them first
-        for (int idx = t; idx < (NP - N) * NP; idx += 256) Vs[(N + idx / NP) * ldp + idx % NP] = 0.0;
+        // moments of the tile (and the stopping test) on the swept values
         __syncthreads();
         unsigned long long dmax = 0ull;
         tile_gemm<NP>(pt, R, Vs, L1, pv, [&](int row, int col, double v, double rv) {
@@ -1018,12 +1070,12 @@ __device__ __forceinline__ void sweep_apply_body(SweepArgs s, bool adjoint, bool
 }
 
 template <int NP>
-__global__ void __launch_bounds__(256) sweep_apply(SweepArgs s, bool adjoint, bool inkernel_carry) {
+__global__ void __launch_bounds__(256, 2) sweep_apply(SweepArgs s, bool adjoint, bool inkernel_carry) {
     sweep_apply_body<NP>(s, adjoint, inkernel_carry, (int)blockIdx.x, (int)blockIdx.y);
 }
 
 template <int NP>
-__global__ void __launch_bounds__(256) sweep_apply_multi(const MultiEntry<SweepArgs> *E, const BlockRef *br, const int *iter) {
+__global__ void __launch_bounds__(256, 2) sweep_apply_multi(const MultiEntry<SweepArgs> *E, const BlockRef *br, const int *iter) {
     const BlockRef r = br[blockIdx.x];
     const MultiEntry<SweepArgs> &e = E[r.entry];
     SweepArgs a = e.a;
