@@ -539,19 +539,20 @@ __device__ __forceinline__ double boundary_inflow(const SweepArgs &s, int n, boo
 // (NP in {16, 32, 64}, NP >= N and NP >= L1) at row stride NP + 1.
 //
 // tile_prefetch / tile_gemm: C = A x B with A [R][NP] and B [NP][NP] in LDS
-// on FP64 MFMA; the four waves take the 16 x 16 output blocks (at most 16)
-// in turn.  tile_prefetch evaluates pre(row, col) for every output position
+// on FP64 MFMA; the four waves take the 16 x 16 output blocks (at most
+// NP / 4) in turn.  tile_prefetch evaluates pre(row, col) for every output position
 // the calling lane will own (clamped to row < R and col < nc, so pre may
 // issue global loads without branches); tile_gemm hands each element with
 // row < R and col < nc to out(row, col, v, pre value).
 template <int NP, class Pre>
-__device__ __forceinline__ void tile_prefetch(int R, int nc, double (&pv)[4][4], Pre &&pre) {
+__device__ __forceinline__ void tile_prefetch(int R, int nc, double (&pv)[NP / 16][4], Pre &&pre) {
     constexpr int NCT = NP / 16;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, kl = lane >> 4;
     const int ntile = ((R + 15) / 16) * NCT;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int t = min(wave + 4 * i, ntile - 1);
+    for (int i = 0; i < NCT; ++i) {
+        const int t = __builtin_amdgcn_readfirstlane(wave + 4 * i);
+        if (t >= ntile) break;
         const int r0 = (t / NCT) * 16, c0 = (t % NCT) * 16;
 #pragma unroll
         for (int r = 0; r < 4; ++r) pv[i][r] = pre(min(r0 + kl + 4 * r, R - 1), min(c0 + (lane & 15), nc - 1));
@@ -562,12 +563,12 @@ __device__ __forceinline__ void tile_prefetch(int R, int nc, double (&pv)[4][4],
 // wave w is output tile w + 4 i), reading A and B only; tile_scatter then
 // hands them to out.  Between the two the caller may reuse A's storage.
 template <int NP>
-__device__ __forceinline__ void tile_products(const double *A, int R, const double *B, d4 (&acc)[4]) {
+__device__ __forceinline__ void tile_products(const double *A, int R, const double *B, d4 (&acc)[NP / 16]) {
     constexpr int NCT = NP / 16, LD = NP + 1, NK = NP / 4;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, kl = lane >> 4;
     const int ntile = ((R + 15) / 16) * NCT;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < NCT; ++i) {
         const int t = wave + 4 * i;
         if (t >= ntile) break;
         const int r0 = (t / NCT) * 16, c0 = (t % NCT) * 16;
@@ -585,12 +586,12 @@ __device__ __forceinline__ void tile_products(const double *A, int R, const doub
 }
 
 template <int NP, class Out>
-__device__ __forceinline__ void tile_scatter(int R, int nc, const d4 (&acc)[4], const double (&pv)[4][4], Out &&out) {
+__device__ __forceinline__ void tile_scatter(int R, int nc, const d4 (&acc)[NP / 16], const double (&pv)[NP / 16][4], Out &&out) {
     constexpr int NCT = NP / 16;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, kl = lane >> 4;
     const int ntile = ((R + 15) / 16) * NCT;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < NCT; ++i) {
         const int t = wave + 4 * i;
         if (t >= ntile) break;
         const int r0 = (t / NCT) * 16, bc = (t % NCT) * 16 + (lane & 15);
@@ -604,30 +605,32 @@ __device__ __forceinline__ void tile_scatter(int R, int nc, const d4 (&acc)[4], 
 
 template <int NP, class Out>
 __device__ __forceinline__ void tile_gemm(const double *A, int R, const double *B, int nc,
-                                          const double (&pv)[4][4], Out &&out) {
-    d4 acc[4];
+                                          const double (&pv)[NP / 16][4], Out &&out) {
+    d4 acc[NP / 16];
     tile_products<NP>(A, R, B, acc);
     tile_scatter<NP>(R, nc, acc, pv, out);
 }
 
-// Copies a rows x NP block into LDS at row stride NP + 1 (rows <= 64, so at
-// most 16 elements per thread): stage_load issues the loads get(r, c) at
+// Copies a rows x NP block into LDS at row stride NP + 1 (rows <= 256 E / NP,
+// E elements per thread): stage_load issues the loads get(r, c) at
 // indices clamped to the block, without branches, stage_store puts the
 // values, 0 where r >= rows_in or c >= cols.  Other loads and work go between.
-template <int NP, class Get>
-__device__ __forceinline__ void stage_load(double (&v)[16], int rows, int cols, Get &&get) {
+template <int NP, int E, class Get>
+__device__ __forceinline__ void stage_load(double (&v)[E], int rows, int cols, Get &&get) {
     const int n = rows * NP, t = threadIdx.x;
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
+    for (int u = 0; u < E; ++u) {
+        if (256 * u >= n) break;
         const int idx = min(t + 256 * u, n - 1);
         v[u] = get(idx / NP, min(idx % NP, cols - 1));
     }
 }
-template <int NP>
-__device__ __forceinline__ void stage_store(double *dst, const double (&v)[16], int rows, int rows_in, int cols) {
+template <int NP, int E>
+__device__ __forceinline__ void stage_store(double *dst, const double (&v)[E], int rows, int rows_in, int cols) {
     const int n = rows * NP, t = threadIdx.x;
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
+    for (int u = 0; u < E; ++u) {
+        if (256 * u >= n) break;
         const int idx = t + 256 * u;
         if (idx < n) dst[(idx / NP) * (NP + 1) + idx % NP] = (idx % NP) < cols && idx / NP < rows_in ? v[u] : 0.0;
     }
@@ -652,15 +655,18 @@ static size_t fused_apply_lds(const SweepArgs &s, int NP) {
 
 // Cells are processed in groups of SWEEP_BATCH: the group's sources and
 // cross sections are loaded before the dependent recurrence runs over it.
+// Loops over a batch end at the sub-chunk's length, the same for the block,
+// since a wave's instructions are what a small tile waits for.
 constexpr int SWEEP_BATCH = 8;
 
 // NP > 0: fused source (q of the tile from phi by MFMA, see SweepArgs).
 //
 // A tile is a chain of latencies, so the loads of every stage go out before
 // the convergence gate is resolved and the first stage waits (wide tiles
-// hold back the last ones for registers: three blocks a CU).  K = 1500,
-// N = 16: 8.2 us with each stage loading for itself, 7.1 now; 32 slabs of
-// 2048 cells, N = 64: 82 and 77.
+// hold back the last ones for registers: three blocks a CU), and a wave
+// issues no more of them than the tile has.  K = 1500, N = 16: 8.2 us with
+// each stage loading for itself, 7.1 with the loads ahead, 4.9 with only
+// those needed; 32 slabs of 2048 cells, N = 64: 82 and 77.
 template <int NP>
 __device__ __forceinline__ void sweep_aggregate_body(SweepArgs s, bool adjoint, const int bx_, const int by_) {
     extern __shared__ double dyn[];
@@ -684,6 +690,7 @@ __device__ __forceinline__ void sweep_aggregate_body(SweepArgs s, bool adjoint, 
     auto load_cells = [&](int i0) {
 #pragma unroll
         for (int u = 0; u < SWEEP_BATCH; ++u) {
+            if (i0 + u >= s.sub) break;
             hh[u] = s.h[cell(i0 + u)];
             st[u] = s.sigma_t[cell(i0 + u)];
         }
@@ -691,6 +698,7 @@ __device__ __forceinline__ void sweep_aggregate_body(SweepArgs s, bool adjoint, 
     auto load_source = [&](int i0) {
 #pragma unroll
         for (int u = 0; u < SWEEP_BATCH; ++u) {
+            if (i0 + u >= s.sub) break;
             const int j = cell(i0 + u);
             if constexpr (fused) {
                 yin[u] = qt[((j - c0) * 2 + in_node) * ldq + n];
@@ -709,7 +717,7 @@ __device__ __forceinline__ void sweep_aggregate_body(SweepArgs s, bool adjoint, 
         double *Bt = At + (size_t)2 * s.TC * ldq;
         const bool has = s.src_qext != nullptr;
         const double *qe = has ? s.src_qext : s.q_out;  // a valid address either way
-        double pv[4][4], va[16], vs[16], vb[16];
+        double pv[NP / 16][4], va[NP / 4], vs[NP / 4], vb[NP * NP / 256];
         auto load_b = [&]() { stage_load<NP>(vb, NP, N, [&](int r, int c) { return s.src_Mt[(size_t)min(r, L1 - 1) * N + c]; }); };
         stage_load<NP>(va, R, L1, [&](int r, int l) { return s.src_phi[((size_t)c0 * 2 + r) * L1 + l]; });
         stage_load<NP>(vs, R, L1, [&](int r, int l) { return s.src_sigma_s[(size_t)(c0 + r / 2) * L1 + l]; });
@@ -717,7 +725,8 @@ __device__ __forceinline__ void sweep_aggregate_body(SweepArgs s, bool adjoint, 
         tile_prefetch<NP>(R, N, pv, [&](int row, int col) { return qe[((size_t)c0 * 2 + row) * N + col]; });
         if (skipped(s.skip)) return;
 #pragma unroll
-        for (int u = 0; u < 16; ++u) va[u] *= vs[u];
+        for (int u = 0; u < NP / 4; ++u)
+            if (256 * u < R * NP) va[u] *= vs[u];
         stage_store<NP>(At, va, R, R, L1);
         if constexpr (wide) {
             load_b();
@@ -725,7 +734,7 @@ __device__ __forceinline__ void sweep_aggregate_body(SweepArgs s, bool adjoint, 
         }
         stage_store<NP>(Bt, vb, NP, L1, N);
         __syncthreads();
-        d4 acc[4];
+        d4 acc[NP / 16];
         tile_products<NP>(At, R, Bt, acc);
         __syncthreads();  // every wave is done reading At, which qt overwrites
         tile_scatter<NP>(R, N, acc, pv, [&](int row, int col, double v, double e) {
@@ -899,7 +908,8 @@ __global__ void __launch_bounds__(64) sweep_scan_carry_multi(const MultiEntry<Sw
 // at the start, before the convergence gate is resolved, and the cells' maps
 // are formed while the block gathers the carry, so the block waits on memory
 // about once before the sweep.  K = 1500, N = 16: 10.0 us with the maps in
-// the recurrence and directions read from mu, 9.4 now.
+// the recurrence and directions read from mu, 9.4 without, 7.4 with staging
+// and batch loops that end where the tile and its runs do.
 // NP > 0: fused moments (and stopping test) of the swept tile, see SweepArgs.
 template <int NP>
 __device__ __forceinline__ void sweep_apply_body(SweepArgs s, bool adjoint, bool inkernel_carry, const int bx_, const int by_) {
@@ -921,10 +931,12 @@ __device__ __forceinline__ void sweep_apply_body(SweepArgs s, bool adjoint, bool
     const int P = dir > 0 ? tile : s.ntiles - 1 - tile;
     const int Q = (P + S - 1) / S;
     const int p0 = sc * Q, p1 = live && inkernel_carry ? min(P, p0 + Q) : 0;
+    const int most = (max(tile, s.ntiles - 1 - tile) + S - 1) / S;  // the longer direction's run
     double ta[16], tb[16];
-    auto load_maps = [&](int i) {
+    auto load_maps = [&](int i, int k) {
 #pragma unroll
         for (int u = 0; u < 16; ++u) {
+            if (k + u >= most) break;
             const int ii = max(min(i + u, p1 - 1), 0);
             const int tt = dir > 0 ? ii : s.ntiles - 1 - ii;
             ta[u] = s.tileA[(size_t)tt * N + n];
@@ -933,7 +945,7 @@ __device__ __forceinline__ void sweep_apply_body(SweepArgs s, bool adjoint, bool
     };
     constexpr bool wide = NP == 64;  // fewer loads ahead: two blocks' registers fit a CU
     if constexpr (!wide)
-        if (p0 < p1) load_maps(p0);
+        if (p0 < p1) load_maps(p0, 0);
     // this tile's sub-chunk aggregates (S x N <= 256 values, one per thread)
     const double sa = live ? s.subA[((size_t)tile * S + sc) * N + n] : 1.0;
     const double sb = live ? s.subB[((size_t)tile * S + sc) * N + n] : 0.0;
@@ -945,6 +957,7 @@ __device__ __forceinline__ void sweep_apply_body(SweepArgs s, bool adjoint, bool
     auto load_batch = [&](int i0) {
 #pragma unroll
         for (int u = 0; u < SWEEP_BATCH; ++u) {
+            if (i0 + u >= s.sub) break;
             const int i = min(i0 + u, max(len - 1, 0));
             const int j = min(dir > 0 ? j0 + i : j1 - 1 - i, s.K - 1);
             yin[u] = s.q[((size_t)j * 2 + in_node) * N + n];
@@ -956,18 +969,18 @@ __device__ __forceinline__ void sweep_apply_body(SweepArgs s, bool adjoint, bool
     load_batch(0);
     // fused: Vt staged, stopping-test references fetched for the tile GEMM,
     // the swept tile's padding columns cleared
-    double pv[4][4];
+    double pv[NP ? NP / 16 : 1][4];
     const int L1 = s.L1, R = 2 * (c1 - c0);
     const bool stop = fused && s.mom_ref != nullptr;
     if constexpr (fused) {
-        double vv[16];
+        double vv[NP * NP / 256];
         stage_load<NP>(vv, NP, L1, [&](int r, int c) { return s.mom_Vt[(size_t)min(r, N - 1) * L1 + c]; });
         const double *ref = stop ? s.mom_ref : s.mom_out;  // a valid address either way
         tile_prefetch<NP>(R, L1, pv, [&](int row, int col) { return ref[((size_t)c0 * 2 + row) * L1 + col]; });
         if (skipped(s.skip)) return;
         stage_store<NP>(Vs, vv, NP, N, L1);
         if constexpr (wide)
-            if (p0 < p1) load_maps(p0);
+            if (p0 < p1) load_maps(p0, 0);
         for (int idx = t; idx < R * (NP - N); idx += 256)
             pt[(idx / (NP - N)) * ldp + N + idx % (NP - N)] = 0.0;
     } else {
@@ -976,7 +989,7 @@ __device__ __forceinline__ void sweep_apply_body(SweepArgs s, bool adjoint, bool
     double x = boundary_inflow(s, n, adjoint);
     double A = 1.0, B = 0.0;
     for (int i = p0; i < p1; i += 16) {
-        if (i > p0) load_maps(i);
+        if (i > p0) load_maps(i, i - p0);
 #pragma unroll
         for (int u = 0; u < 16; ++u) {
             if (i + u < p1) {
