@@ -151,6 +151,7 @@ struct Workspace {
     double *fvec = nullptr, *gvec = nullptr, *bvec = nullptr;
     double *part_f = nullptr, *part_b = nullptr;
     double *subA = nullptr, *subB = nullptr, *tileA = nullptr, *tileB = nullptr;
+    double *nextA = nullptr, *nextB = nullptr;  // source iteration: the other iteration's tile maps
     double *carry = nullptr, *sweep_exit = nullptr;
     double *grpA = nullptr, *grpB = nullptr;
     unsigned long long *hist = nullptr;       // device, per-iteration stopping-test values
@@ -1577,6 +1578,8 @@ sn_status sn_setup(const sn_problem_desc *d, void *stream, sn_handle *out) {
                 W.subB = H->dalloc<double>(ws_sub);
                 W.tileA = H->dalloc<double>(ws_tile);
                 W.tileB = H->dalloc<double>(ws_tile);
+                W.nextA = H->dalloc<double>(ws_tile);
+                W.nextB = H->dalloc<double>(ws_tile);
                 W.carry = H->dalloc<double>(ws_tile);
                 W.grpA = H->dalloc<double>(ws_grp);
                 W.grpB = H->dalloc<double>(ws_grp);
@@ -2053,6 +2056,16 @@ static sn_status solve_impl(sn_handle h, int32_t method, double tol, int32_t max
                         a.mom_out = W.phi_half;
                     } else {
                         a.mom_out = nxt; a.mom_ref = cur; a.mom_slot = fs.slot;
+                        if (sweep_steps(a)) {
+                            a.nextA = W.nextA;
+                            a.nextB = W.nextB;
+                            if (!(m & 1)) {
+                                std::swap(a.tileA, a.nextA);
+                                std::swap(a.tileB, a.nextB);
+                            }
+                            launch_sweep_step(a, m == 1, sg, h->timer);
+                            continue;
+                        }
                     }
                     launch_sweep(a, false, sg, h->timer);
                     if (method == SN_FPSA) {

@@ -497,28 +497,28 @@ void launch_gemm(const GemmArgs &g, hipStream_t s, KernelTimer *t) {
 // ---------------------------------------------------------------------------
 constexpr int SWEEP_INKERNEL_TILES = 128;
 
-// The cell's two maps of its inflow x: outflow a x + b, inflow-side node
-// p x + r.  Needs no inflow, so it is formed before the block waits for one.
-struct CellCoef {
-    double a, b, p, r;
+// The cell's maps of its inflow x, outflow a x + b and inflow-side node
+// p x + r: a and p need neither the inflow nor the sources, so they are
+// formed before the block waits for either.
+struct CellMap {
+    double a, p, w, f;
+    __device__ __forceinline__ double b(double gin, double gout) const { return p * gout + a * gin; }
+    __device__ __forceinline__ double r(double gin, double gout) const { return p * gin - w * gout; }
 };
 
-__device__ __forceinline__ CellCoef cell_coef(double inv_absmu, double hj, double stj,
-                                              double yin, double yout, bool adjoint) {
+__device__ __forceinline__ CellMap cell_map(double inv_absmu, double hj, double stj) {
     const double tau = stj * hj * inv_absmu;
     const double di = 1.0 / (6.0 + tau * (4.0 + tau));
-    double gin = yin, gout = yout;
-    if (!adjoint) {
-        const double f = hj * inv_absmu * (1.0 / 6.0);
-        gin = f * (2.0 * yin + yout);
-        gout = f * (yin + 2.0 * yout);
-    }
-    CellCoef c;
+    CellMap c;
     c.a = (6.0 - 2.0 * tau) * di;
-    c.b = ((6.0 + 4.0 * tau) * gout + (6.0 - 2.0 * tau) * gin) * di;
     c.p = (6.0 + 4.0 * tau) * di;
-    c.r = ((6.0 + 4.0 * tau) * gin - (6.0 + 2.0 * tau) * gout) * di;
+    c.w = (6.0 + 2.0 * tau) * di;
+    c.f = hj * inv_absmu * (1.0 / 6.0);
     return c;
+}
+__device__ __forceinline__ void cell_sources(const CellMap &c, double yin, double yout, bool adjoint, double &gin, double &gout) {
+    gin = adjoint ? yin : c.f * (2.0 * yin + yout);
+    gout = adjoint ? yout : c.f * (yin + 2.0 * yout);
 }
 
 // Direction of the recurrence for angle n: +1 left-to-right, -1 right-to-left.
@@ -636,6 +636,19 @@ __device__ __forceinline__ void stage_store(double *dst, const double (&v)[E], i
     }
 }
 
+// Multiplies a block in LDS by values staged with stage_load (0 past the
+// columns stays 0: those columns hold 0).
+template <int NP, int E>
+__device__ __forceinline__ void scale_rows(double *A, int rows, const double (&v)[E]) {
+    const int n = rows * NP, t = threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < E; ++u) {
+        if (256 * u >= n) break;
+        const int idx = t + 256 * u;
+        if (idx < n) A[(idx / NP) * (NP + 1) + idx % NP] *= v[u];
+    }
+}
+
 // padded width of a fusable slab, 0 if the sweep cannot carry the GEMMs
 static int fuse_width(int N, int L1, int TC) {
     if (N < 8 || N > 64 || L1 > 64 || TC > 32) return 0;
@@ -658,6 +671,20 @@ static size_t fused_apply_lds(const SweepArgs &s, int NP) {
 // Loops over a batch end at the sub-chunk's length, the same for the block,
 // since a wave's instructions are what a small tile waits for.
 constexpr int SWEEP_BATCH = 8;
+
+// The tile's map from its sub-chunks' (in LDS, [S][N]).
+__device__ __forceinline__ void compose_tile(const SweepArgs &s, const double *shA, const double *shB, int tile, int n,
+                                             int dir, double *outA, double *outB) {
+    double TA = 1.0, TB = 0.0;
+    for (int i = 0; i < s.S; ++i) {
+        const int ss = dir > 0 ? i : s.S - 1 - i;
+        const double a = shA[ss * s.N + n], b = shB[ss * s.N + n];
+        TB = a * TB + b;
+        TA = a * TA;
+    }
+    outA[(size_t)tile * s.N + n] = TA;
+    outB[(size_t)tile * s.N + n] = TB;
+}
 
 // NP > 0: fused source (q of the tile from phi by MFMA, see SweepArgs).
 //
@@ -754,8 +781,10 @@ __device__ __forceinline__ void sweep_aggregate_body(SweepArgs s, bool adjoint, 
 #pragma unroll
             for (int u = 0; u < SWEEP_BATCH; ++u) {
                 if (i0 + u < len) {
-                    const CellCoef c = cell_coef(inv, hh[u], st[u], yin[u], yout[u], adjoint);
-                    B = c.a * B + c.b;
+                    double gin, gout;
+                    const CellMap c = cell_map(inv, hh[u], st[u]);
+                    cell_sources(c, yin[u], yout[u], adjoint, gin, gout);
+                    B = c.a * B + c.b(gin, gout);
                     A = c.a * A;
                 }
             }
@@ -766,17 +795,7 @@ __device__ __forceinline__ void sweep_aggregate_body(SweepArgs s, bool adjoint, 
     shA[t] = A;
     shB[t] = B;
     __syncthreads();
-    if (sc == 0) {
-        double TA = 1.0, TB = 0.0;
-        for (int i = 0; i < S; ++i) {
-            const int ss = dir > 0 ? i : S - 1 - i;
-            const double a = shA[ss * N + n], b = shB[ss * N + n];
-            TB = a * TB + b;
-            TA = a * TA;
-        }
-        s.tileA[(size_t)tile * N + n] = TA;
-        s.tileB[(size_t)tile * N + n] = TB;
-    }
+    if (sc == 0) compose_tile(s, shA, shB, tile, n, dir, s.tileA, s.tileB);
 }
 
 template <int NP>
@@ -911,7 +930,14 @@ __global__ void __launch_bounds__(64) sweep_scan_carry_multi(const MultiEntry<Sw
 // the recurrence and directions read from mu, 9.4 without, 7.4 with staging
 // and batch loops that end where the tile and its runs do.
 // NP > 0: fused moments (and stopping test) of the swept tile, see SweepArgs.
-template <int NP>
+//
+// NEXT (source iteration): the block goes on to the next iteration's
+// aggregate pass of its tile, whose scattering source needs only the moments
+// that it has just formed, so an iteration is one launch; the tile maps go
+// to nextA / nextB, as other blocks still read this iteration's.  Measured
+// per iteration against the two launches (us): K = 1500, N = 16 9.3 (13.4);
+// K = 2000, N = 64 17 (23); K = 4000, N = 64 25.5 (27.6).
+template <int NP, bool NEXT>
 __device__ __forceinline__ void sweep_apply_body(SweepArgs s, bool adjoint, bool inkernel_carry, const int bx_, const int by_) {
     extern __shared__ double dyn[];
     __shared__ double shA[256], shB[256], subA[256], subB[256];
@@ -972,9 +998,30 @@ __device__ __forceinline__ void sweep_apply_body(SweepArgs s, bool adjoint, bool
     double pv[NP ? NP / 16 : 1][4];
     const int L1 = s.L1, R = 2 * (c1 - c0);
     const bool stop = fused && s.mom_ref != nullptr;
+    // NEXT: operands of the next source
+    double vs[NEXT ? NP / 4 : 1], vb[NEXT ? NP * NP / 256 : 1], qv[NEXT ? NP / 16 : 1][4];
+    [[maybe_unused]] auto load_scale = [&]() {
+        if constexpr (NEXT)
+            stage_load<NP>(vs, R, L1, [&](int r, int l) { return s.src_sigma_s[(size_t)(c0 + r / 2) * L1 + l]; });
+    };
+    [[maybe_unused]] auto load_mt = [&]() {
+        if constexpr (NEXT)
+            stage_load<NP>(vb, NP, N, [&](int r, int c) { return s.src_Mt[(size_t)min(r, L1 - 1) * N + c]; });
+    };
+    [[maybe_unused]] auto load_qext = [&]() {
+        if constexpr (NEXT) {
+            const double *qe = s.src_qext ? s.src_qext : s.q_out;  // a valid address either way
+            tile_prefetch<NP>(R, N, qv, [&](int row, int col) { return qe[((size_t)c0 * 2 + row) * N + col]; });
+        }
+    };
     if constexpr (fused) {
         double vv[NP * NP / 256];
         stage_load<NP>(vv, NP, L1, [&](int r, int c) { return s.mom_Vt[(size_t)min(r, N - 1) * L1 + c]; });
+        if constexpr (NEXT && !wide) {
+            load_mt();
+            load_scale();
+            load_qext();
+        }
         const double *ref = stop ? s.mom_ref : s.mom_out;  // a valid address either way
         tile_prefetch<NP>(R, L1, pv, [&](int row, int col) { return ref[((size_t)c0 * 2 + row) * L1 + col]; });
         if (skipped(s.skip)) return;
@@ -1003,16 +1050,17 @@ __device__ __forceinline__ void sweep_apply_body(SweepArgs s, bool adjoint, bool
     subA[t] = sa;
     subB[t] = sb;
     // the first batch's maps, formed while the block gathers
-    double ca[SWEEP_BATCH], cb[SWEEP_BATCH], cp[SWEEP_BATCH], cr[SWEEP_BATCH];
+    CellMap cm[SWEEP_BATCH];
+    double cb[SWEEP_BATCH], cr[SWEEP_BATCH];
     auto maps = [&](int i0) {
 #pragma unroll
         for (int u = 0; u < SWEEP_BATCH; ++u) {
             if (i0 + u < len) {
-                const CellCoef c = cell_coef(inv, hh[u], st[u], yin[u], yout[u], adjoint);
-                ca[u] = c.a;
-                cb[u] = c.b;
-                cp[u] = c.p;
-                cr[u] = c.r;
+                double gin, gout;
+                cm[u] = cell_map(inv, hh[u], st[u]);
+                cell_sources(cm[u], yin[u], yout[u], adjoint, gin, gout);
+                cb[u] = cm[u].b(gin, gout);
+                cr[u] = cm[u].r(gin, gout);
             }
         }
     };
@@ -1045,11 +1093,11 @@ __device__ __forceinline__ void sweep_apply_body(SweepArgs s, bool adjoint, bool
                     const int j = dir > 0 ? j0 + i0 + u : j1 - 1 - i0 - u;
                     const size_t iin = ((size_t)j * 2 + in_node) * N + n;
                     const size_t iout = ((size_t)j * 2 + (1 - in_node)) * N + n;
-                    const double vout = ca[u] * x + cb[u];
-                    const double vin = cp[u] * x + cr[u];
+                    const double vout = cm[u].a * x + cb[u];
+                    const double vin = cm[u].p * x + cr[u];
                     if (adjoint) {
                         // x = (h/(6|mu|)) [[2,1],[1,2]] zeta  (node order in/out is symmetric)
-                        const double f = hh[u] * inv * (1.0 / 6.0);
+                        const double f = cm[u].f;
                         s.psi[iin] = f * (2.0 * vin + vout);
                         s.psi[iout] = f * (vin + 2.0 * vout);
                     } else {
@@ -1071,20 +1119,75 @@ __device__ __forceinline__ void sweep_apply_body(SweepArgs s, bool adjoint, bool
         // moments of the tile (and the stopping test) on the swept values
         __syncthreads();
         unsigned long long dmax = 0ull;
-        tile_gemm<NP>(pt, R, Vs, L1, pv, [&](int row, int col, double v, double rv) {
+        auto moment = [&](int row, int col, double v, double rv) {
             s.mom_out[((size_t)c0 * 2 + row) * L1 + col] = v;
             if (stop) {
                 const unsigned long long d = absdiff_bits(v, rv);
                 dmax = d > dmax ? d : dmax;
             }
-        });
-        if (stop) stop_block_reduce(dmax, s.mom_slot);
+        };
+        if constexpr (!NEXT) {
+            tile_gemm<NP>(pt, R, Vs, L1, pv, moment);
+            if (stop) stop_block_reduce(dmax, s.mom_slot);
+        } else {
+            if constexpr (wide) load_mt();
+            d4 acc[NP / 16];
+            tile_products<NP>(pt, R, Vs, acc);
+            __syncthreads();  // the swept tile and Vs are read: sigma_s phi and Mt take their place
+            tile_scatter<NP>(R, L1, acc, pv, [&](int row, int col, double v, double rv) {
+                moment(row, col, v, rv);
+                pt[row * ldp + col] = v;
+            });
+            for (int idx = t; idx < R * (NP - L1); idx += 256) pt[(idx / (NP - L1)) * ldp + L1 + idx % (NP - L1)] = 0.0;
+            stage_store<NP>(Vs, vb, NP, L1, N);
+            if constexpr (wide) load_scale();
+            __syncthreads();
+            if (stop) stop_block_reduce(dmax, s.mom_slot);
+            scale_rows<NP>(pt, R, vs);
+            if constexpr (wide) load_qext();
+            __syncthreads();
+            tile_products<NP>(pt, R, Vs, acc);
+            __syncthreads();
+            const bool has = s.src_qext != nullptr;
+            tile_scatter<NP>(R, N, acc, qv, [&](int row, int col, double v, double e) {
+                v += has ? e : 0.0;
+                pt[row * ldp + col] = v;
+                s.q_out[((size_t)c0 * 2 + row) * N + col] = v;
+            });
+            __syncthreads();
+            double A1 = 1.0, B1 = 0.0;
+            if (live) {
+                // one batch (TC <= 32 and S >= 4: at most 8 cells), its maps still in cm
+#pragma unroll
+                for (int u = 0; u < SWEEP_BATCH; ++u) {
+                    if (u < len) {
+                        const int j = dir > 0 ? j0 + u : j1 - 1 - u;
+                        const double y0 = pt[((j - c0) * 2 + in_node) * ldp + n], y1 = pt[((j - c0) * 2 + (1 - in_node)) * ldp + n];
+                        double gin, gout;
+                        cell_sources(cm[u], y0, y1, false, gin, gout);
+                        B1 = cm[u].a * B1 + cm[u].b(gin, gout);
+                        A1 = cm[u].a * A1;
+                    }
+                }
+                s.subA[((size_t)tile * S + sc) * N + n] = A1;
+                s.subB[((size_t)tile * S + sc) * N + n] = B1;
+            }
+            shA[t] = A1;
+            shB[t] = B1;
+            __syncthreads();
+            if (sc == 0) compose_tile(s, shA, shB, tile, n, dir, s.nextA, s.nextB);
+        }
     }
 }
 
 template <int NP>
 __global__ void __launch_bounds__(256, 2) sweep_apply(SweepArgs s, bool adjoint, bool inkernel_carry) {
-    sweep_apply_body<NP>(s, adjoint, inkernel_carry, (int)blockIdx.x, (int)blockIdx.y);
+    sweep_apply_body<NP, false>(s, adjoint, inkernel_carry, (int)blockIdx.x, (int)blockIdx.y);
+}
+
+template <int NP>
+__global__ void __launch_bounds__(256, 2) sweep_step(SweepArgs s) {
+    sweep_apply_body<NP, true>(s, false, true, (int)blockIdx.x, 0);
 }
 
 template <int NP>
@@ -1093,7 +1196,7 @@ __global__ void __launch_bounds__(256, 2) sweep_apply_multi(const MultiEntry<Swe
     const MultiEntry<SweepArgs> &e = E[r.entry];
     SweepArgs a = e.a;
     apply_patch(a, e.p, *iter);
-    sweep_apply_body<NP>(a, false, e.flag != 0, r.local, 0);
+    sweep_apply_body<NP, false>(a, false, e.flag != 0, r.local, 0);
 }
 
 
@@ -1180,6 +1283,31 @@ void launch_sweep(const SweepArgs &s0, bool adjoint, hipStream_t st, KernelTimer
                 }
                 break;
         }
+    }
+}
+
+bool sweep_steps(const SweepArgs &s) {
+    return fuse_width(s.N, s.L1, s.TC) > 0 && s.ntiles <= SWEEP_INKERNEL_TILES;
+}
+
+void launch_sweep_step(const SweepArgs &s, bool first, hipStream_t st, KernelTimer *t) {
+    if (s.K <= 0) return;
+    LaunchShape sh[4];
+    const int n = sweep_shapes(s, sh);
+    const LaunchShape &a = sh[0], &p = sh[n - 1];
+    switch (p.v1) {
+        case 16:
+            if (first) launch_sweep_agg<16>(a, s, false, st, t);
+            LAUNCH(p.kid, t, sweep_step<16>, dim3(p.gx), dim3(256), p.lds, st, s);
+            break;
+        case 32:
+            if (first) launch_sweep_agg<32>(a, s, false, st, t);
+            LAUNCH(p.kid, t, sweep_step<32>, dim3(p.gx), dim3(256), p.lds, st, s);
+            break;
+        default:
+            if (first) launch_sweep_agg<64>(a, s, false, st, t);
+            LAUNCH(p.kid, t, sweep_step<64>, dim3(p.gx), dim3(256), p.lds, st, s);
+            break;
     }
 }
 

@@ -69,6 +69,8 @@ struct SweepArgs {
     const double *mom_ref = nullptr;
     unsigned long long *mom_slot = nullptr;
     bool write_psi = true;
+    // tile maps of the next iteration (launch_sweep_step): [ntiles][N], not tileA / tileB
+    double *nextA = nullptr, *nextB = nullptr;
 };
 
 // Whether a slab's sweep can carry the fused source / moments GEMMs.
@@ -311,6 +313,10 @@ void launch_iter_step(int *iter, hipStream_t s);
 
 void launch_gemm(const GemmArgs &g, hipStream_t s, KernelTimer *t);
 void launch_sweep(const SweepArgs &a, bool adjoint, hipStream_t s, KernelTimer *t);
+// Whether source iteration may take one launch an iteration, and that launch
+// (with first: after the aggregate pass of the first iterate).
+bool sweep_steps(const SweepArgs &a);
+void launch_sweep_step(const SweepArgs &a, bool first, hipStream_t s, KernelTimer *t);
 // *slot = max |a - b| (IEEE bits, atomicMax); gated by skip.
 void launch_stopping_test(const double *a, const double *b, size_t n, unsigned long long *slot,
                           SkipTest skip, hipStream_t s, KernelTimer *t);
