@@ -1998,7 +1998,7 @@ static sn_status solve_impl(sn_handle h, int32_t method, double tol, int32_t max
     // passes on the device the remaining queued iterations do nothing.  The
     // batch size follows the observed contraction rate.
     struct SlotRun {
-        int slab = -1, launched = 0, batch = 2, its = 0, pending = 0;
+        int slab = -1, launched = 0, batch = 4, its = 0, pending = 0;
         bool nonfinite = false;
     };
     const int G = std::min<int>((int)h->ws.size(), (int)h->slabs.size());
@@ -2107,7 +2107,10 @@ static sn_status solve_impl(sn_handle h, int32_t method, double tol, int32_t max
             }
             r.launched += nb;
             if (r.its || r.launched >= max_iter) return true;
-            // predict the iterations still needed from the recent contraction rate
+            // predict the iterations still needed from the recent contraction
+            // rate, and one more: a read-back leaves the GPU idle for about
+            // 30 us, an iteration too many costs its gated launches (about
+            // 2 us each)
             double hl, h0;
             std::memcpy(&hl, &W.hist_host[r.launched - 1], sizeof(double));
             const int d = std::min(r.launched - 1, 8);
@@ -2117,7 +2120,7 @@ static sn_status solve_impl(sn_handle h, int32_t method, double tol, int32_t max
                 const double rho = std::pow(hl / h0, 1.0 / d);
                 if (rho > 0.0 && rho < 1.0 && hl > tol) {
                     const double rem = std::log(tol / hl) / std::log(rho);
-                    nextb = (int)std::min(4096.0, std::max(1.0, std::ceil(0.9 * rem)));
+                    nextb = (int)std::min(4096.0, std::max(1.0, std::ceil(rem) + 1.0));
                 }
             }
             r.batch = nextb;
