@@ -715,6 +715,7 @@ static void plan_group(const std::vector<const PlanItem *> &items, const A PlanI
         ent[i].p = v[i]->p;
         ent[i].gx = v[i]->sh.gx;
         ent[i].flag = v[i]->sh.v2;
+        ent[i].v1 = v[i]->sh.v1;
         maxb = std::max(maxb, v[i]->sh.gx * v[i]->sh.gy);
         lds = std::max(lds, v[i]->sh.lds);
     }
@@ -730,6 +731,11 @@ static void plan_group(const std::vector<const PlanItem *> &items, const A PlanI
     };
     MultiLaunch L;
     L.shape = v[0]->sh;
+    for (const PlanItem *it : v)
+        if (it->sh.v1 != L.shape.v1) {
+            L.shape.v1 = kMixedWidths;
+            break;
+        }
     L.nblocks = (int)refs.size();
     L.lds = lds;
     const size_t e_off = put(ent.data(), ent.size() * sizeof(MultiEntry<A>));
@@ -990,6 +996,28 @@ static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool pro
             const LaunchShape &s = items[i].sh;
             if (s.gx * s.gy <= 0) continue;
             groups[std::make_tuple(s.kernel, s.v1, s.v2, s.block)].push_back(&items[i]);
+        }
+        // widths of few blocks go in one launch (kMixedBlocks)
+        for (auto kv = groups.begin(); kv != groups.end(); ++kv) {
+            const int kernel = std::get<0>(kv->first), v1 = std::get<1>(kv->first);
+            if (v1 == 0 || (kernel != MK_SWEEP_AGG && kernel != MK_SWEEP_APPLY && kernel != MK_FPT)) continue;
+            auto same = [&](const auto &o) {
+                return std::get<0>(o->first) == kernel && std::get<1>(o->first) != 0 &&
+                       std::get<2>(o->first) == std::get<2>(kv->first) && std::get<3>(o->first) == std::get<3>(kv->first);
+            };
+            int blocks = 0;
+            for (auto o = kv; o != groups.end(); ++o)
+                if (same(o))
+                    for (const PlanItem *it : o->second) blocks += it->sh.gx * it->sh.gy;
+            if (blocks > kMixedBlocks) continue;
+            for (auto o = std::next(kv); o != groups.end();) {
+                if (!same(o)) {
+                    ++o;
+                    continue;
+                }
+                kv->second.insert(kv->second.end(), o->second.begin(), o->second.end());
+                o = groups.erase(o);
+            }
         }
         for (auto &kv : groups) {
             switch (kv.second[0]->kind) {

@@ -432,16 +432,34 @@ __global__ void __launch_bounds__(FPT_T) fpt_kernel(FPTreeArgs f) {
     fpt_body<MODE, NB>(f, (int)blockIdx.x);
 }
 
+__device__ __forceinline__ void apply_patch(FPTreeArgs &a, const IterPatch &p, int m) {
+    patch_skip(a.skip, p, m);
+    if (p.flags & PATCH_A1SUB_CUR) a.old = iter_buf(p, m - 1);
+    if (p.flags & PATCH_C_NXT) a.out = iter_buf(p, m);
+    if (p.flags & PATCH_STOP) a.stop_slot = iter_slot(p, m);
+}
+
 template <int MODE, int NB>
 __global__ void __launch_bounds__(FPT_T) fpt_kernel_multi(const MultiEntry<FPTreeArgs> *E, const BlockRef *br, const int *iter) {
     const BlockRef r = br[blockIdx.x];
     const MultiEntry<FPTreeArgs> &e = E[r.entry];
     FPTreeArgs a = e.a;
-    patch_skip(a.skip, e.p, *iter);
-    if (e.p.flags & PATCH_A1SUB_CUR) a.old = iter_buf(e.p, *iter - 1);
-    if (e.p.flags & PATCH_C_NXT) a.out = iter_buf(e.p, *iter);
-    if (e.p.flags & PATCH_STOP) a.stop_slot = iter_slot(e.p, *iter);
+    apply_patch(a, e.p, *iter);
     fpt_body<MODE, NB>(a, r.local);
+}
+
+// Entries of several widths in one launch (kMixedBlocks).
+template <int MODE>
+__global__ void __launch_bounds__(FPT_T) fpt_kernel_mixed(const MultiEntry<FPTreeArgs> *E, const BlockRef *br, const int *iter) {
+    const BlockRef r = br[blockIdx.x];
+    const MultiEntry<FPTreeArgs> &e = E[r.entry];
+    FPTreeArgs a = e.a;
+    apply_patch(a, e.p, *iter);
+    switch (e.v1) {
+        case 2: fpt_body<MODE, 2>(a, r.local); break;
+        case 4: fpt_body<MODE, 4>(a, r.local); break;
+        default: fpt_body<MODE, 8>(a, r.local); break;
+    }
 }
 
 constexpr int kFptModes[] = {FPT_LEAF | FPT_UP, FPT_UP, FPT_UP | FPT_ROOT | FPT_DOWN, FPT_DOWN, FPT_DOWN | FPT_UPDATE,
@@ -485,15 +503,17 @@ void launch_fpt(const FPTreeArgs &f, int mode, hipStream_t s, KernelTimer *t) {
     switch (sh.v1) {
         case 2: fpt_launch_nb<2>(sh, f, s, t); break;
         case 4: fpt_launch_nb<4>(sh, f, s, t); break;
-        case 8: fpt_launch_nb<8>(sh, f, s, t); break;
-        default: fpt_launch_nb<16>(sh, f, s, t); break;
+        default: fpt_launch_nb<8>(sh, f, s, t); break;
     }
 }
 
 template <int M, int NB>
 static void fpt_multi_m(const MultiLaunch &L, const int *iter, hipStream_t s, KernelTimer *t) {
-    LAUNCH(L.shape.kid, t, (fpt_kernel_multi<M, NB>), dim3(L.nblocks), dim3(FPT_T), L.lds, s,
-           static_cast<const MultiEntry<FPTreeArgs> *>(L.entries), L.refs, iter);
+    const MultiEntry<FPTreeArgs> *E = static_cast<const MultiEntry<FPTreeArgs> *>(L.entries);
+    if constexpr (NB == kMixedWidths)
+        LAUNCH(L.shape.kid, t, fpt_kernel_mixed<M>, dim3(L.nblocks), dim3(FPT_T), L.lds, s, E, L.refs, iter);
+    else
+        LAUNCH(L.shape.kid, t, (fpt_kernel_multi<M, NB>), dim3(L.nblocks), dim3(FPT_T), L.lds, s, E, L.refs, iter);
 }
 
 template <int NB>
@@ -512,8 +532,8 @@ void launch_fpt_multi(const MultiLaunch &L, const int *iter, hipStream_t s, Kern
     switch (L.shape.v1) {
         case 2: fpt_multi_nb<2>(L, iter, s, t); break;
         case 4: fpt_multi_nb<4>(L, iter, s, t); break;
-        case 8: fpt_multi_nb<8>(L, iter, s, t); break;
-        default: fpt_multi_nb<16>(L, iter, s, t); break;
+        case kMixedWidths: fpt_multi_nb<kMixedWidths>(L, iter, s, t); break;
+        default: fpt_multi_nb<8>(L, iter, s, t); break;
     }
 }
 

@@ -803,6 +803,19 @@ __global__ void __launch_bounds__(256, 2) sweep_aggregate(SweepArgs s, bool adjo
     sweep_aggregate_body<NP>(s, adjoint, (int)blockIdx.x, (int)blockIdx.y);
 }
 
+// Entries of several padded widths in one launch (kMixedBlocks).
+__global__ void __launch_bounds__(256, 2) sweep_aggregate_mixed(const MultiEntry<SweepArgs> *E, const BlockRef *br, const int *iter) {
+    const BlockRef r = br[blockIdx.x];
+    const MultiEntry<SweepArgs> &e = E[r.entry];
+    SweepArgs a = e.a;
+    apply_patch(a, e.p, *iter);
+    switch (e.v1) {
+        case 16: sweep_aggregate_body<16>(a, false, r.local, 0); break;
+        case 32: sweep_aggregate_body<32>(a, false, r.local, 0); break;
+        default: sweep_aggregate_body<64>(a, false, r.local, 0); break;
+    }
+}
+
 template <int NP>
 __global__ void __launch_bounds__(256, 2) sweep_aggregate_multi(const MultiEntry<SweepArgs> *E, const BlockRef *br, const int *iter) {
     const BlockRef r = br[blockIdx.x];
@@ -1188,6 +1201,18 @@ __global__ void __launch_bounds__(256, 2) sweep_apply(SweepArgs s, bool adjoint,
 template <int NP>
 __global__ void __launch_bounds__(256, 2) sweep_step(SweepArgs s) {
     sweep_apply_body<NP, true>(s, false, true, (int)blockIdx.x, 0);
+}
+
+__global__ void __launch_bounds__(256, 2) sweep_apply_mixed(const MultiEntry<SweepArgs> *E, const BlockRef *br, const int *iter) {
+    const BlockRef r = br[blockIdx.x];
+    const MultiEntry<SweepArgs> &e = E[r.entry];
+    SweepArgs a = e.a;
+    apply_patch(a, e.p, *iter);
+    switch (e.v1) {
+        case 16: sweep_apply_body<16, false>(a, false, e.flag != 0, r.local, 0); break;
+        case 32: sweep_apply_body<32, false>(a, false, e.flag != 0, r.local, 0); break;
+        default: sweep_apply_body<64, false>(a, false, e.flag != 0, r.local, 0); break;
+    }
 }
 
 template <int NP>
@@ -2713,6 +2738,7 @@ void launch_multi(const MultiLaunch &L, const int *iter, hipStream_t s, KernelTi
         case MK_SWEEP_AGG: {
             const MultiEntry<SweepArgs> *E = multi_entries<SweepArgs>(L);
             switch (sh.v1) {
+                case kMixedWidths: LAUNCH(sh.kid, t, sweep_aggregate_mixed, grid, dim3(256), L.lds, s, E, L.refs, iter); break;
                 case 16: LAUNCH(sh.kid, t, sweep_aggregate_multi<16>, grid, dim3(256), L.lds, s, E, L.refs, iter); break;
                 case 32: LAUNCH(sh.kid, t, sweep_aggregate_multi<32>, grid, dim3(256), L.lds, s, E, L.refs, iter); break;
                 case 64: LAUNCH(sh.kid, t, sweep_aggregate_multi<64>, grid, dim3(256), L.lds, s, E, L.refs, iter); break;
@@ -2729,6 +2755,7 @@ void launch_multi(const MultiLaunch &L, const int *iter, hipStream_t s, KernelTi
         case MK_SWEEP_APPLY: {
             const MultiEntry<SweepArgs> *E = multi_entries<SweepArgs>(L);
             switch (sh.v1) {
+                case kMixedWidths: LAUNCH(sh.kid, t, sweep_apply_mixed, grid, dim3(256), L.lds, s, E, L.refs, iter); break;
                 case 16: LAUNCH(sh.kid, t, sweep_apply_multi<16>, grid, dim3(256), L.lds, s, E, L.refs, iter); break;
                 case 32: LAUNCH(sh.kid, t, sweep_apply_multi<32>, grid, dim3(256), L.lds, s, E, L.refs, iter); break;
                 case 64: LAUNCH(sh.kid, t, sweep_apply_multi<64>, grid, dim3(256), L.lds, s, E, L.refs, iter); break;

@@ -222,6 +222,7 @@ struct MultiEntry {
     IterPatch p;
     int gx = 1;    // blocks in x of the entry's own grid
     int flag = 0;  // sweep apply: the carry-in is formed in the kernel
+    int v1 = 0;    // kernel variant of the entry (LaunchShape::v1), for mixed launches
 };
 
 // Stopping test of one slab (eq:iterate): *slot = max |a - b| over n values.
@@ -277,6 +278,14 @@ enum MultiKernel {
 // the tree's kernels: ascent from the cells, ascent of a later stage, the
 // root chunk, descent, descent with the update, and all of it in one chunk
 enum FptKernel { FPT_K_LEAF_UP = 0, FPT_K_UP, FPT_K_ROOT, FPT_K_DOWN, FPT_K_UPDATE, FPT_K_ALL };
+constexpr int kMixedWidths = -1;  // LaunchShape::v1: each entry has its own variant
+// A phase's launches of several widths become one while they have at most
+// four blocks per CU together: each is bound by its latency then, and they
+// run side by side.  16 slabs of N = 16, 32 and 64, us an iteration apart and
+// together: aggregate passes 20.5 / 8.6, apply passes 23.4 / 9.3, tree
+// launches 107 / 76.  With more blocks a mixed launch's narrow ones would
+// be held back by the widest's registers and LDS.
+constexpr int kMixedBlocks = 1024;
 struct LaunchShape {
     int kernel = 0, v1 = 0, v2 = 0;
     int gx = 1, gy = 1;
