@@ -609,7 +609,9 @@ static bool tree_stages(int K, int N, int L2, int slabs, const std::vector<int> 
             whole = std::max(whole, u + d);
         }
         const double rows_us = (double)rows * (N + (leaf ? 2 * L2 : 0)) * 8 * kTreeUsPerByte;
-        const double rounds = std::max(1.0, (double)chunks * slabs / kTreeCus);
+        // more chunks than CUs: rounds, which overlap where two blocks fit a CU
+        const bool two = tree_lds(N, L2, rows, leaf, root) * sizeof(double) <= kTreeLdsTwo;
+        const double rounds = std::max(1.0, (double)chunks * slabs / kTreeCus * (two ? 0.7 : 1.0));
         return root ? kTreeUsPerLaunch + rounds * (whole + rows_us)
                     : 2 * kTreeUsPerLaunch + rounds * (up + down + 2 * rows_us);
     };

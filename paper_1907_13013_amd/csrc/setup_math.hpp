@@ -92,7 +92,7 @@ constexpr int kTreeMaxStages = 5, kTreeLv = 12, kTreeMaxPasses = 128;
 constexpr int kTreeWaves = 8;         // waves of a chunk's block
 constexpr int kTreeHdr = 20, kTreeMaxUnits = 128;
 constexpr int kTreeMaxRows = 255, kTreeMaxLevels = 8;
-constexpr size_t kTreeLdsBytes = 148 << 10;
+constexpr size_t kTreeLdsBytes = 148 << 10, kTreeLdsTwo = 78 << 10;
 // Cost model of the cut into stages (microseconds): a launch with its gap, a
 // level's barriers and bookkeeping, a byte of matrices into one CU (measured
 // 100 to 134 GB/s), a cycle of FP64 MFMA on one of a CU's four SIMDs at 2.39 GHz.

@@ -18,9 +18,11 @@
 //
 // What bounds it: a level is a barrier, its bookkeeping and a stream of N x 2N
 // (up) or N x N (down) doubles per class into the chunk's one CU, about 1.3
-// and 1.0 us for one class at N = 64; a launch is about 3 us more.  Large batches are
-// bounded by issue (7 vector and 4 scalar instructions per MFMA) and memory
-// latency with one or two blocks of 8 waves per CU: 24 % of the MFMA rate.
+// and 1.0 us for one class at N = 64; a launch is about 3 us more.  Large
+// batches are bounded by issue (7 vector and 4 scalar instructions per MFMA)
+// and latency: two blocks of 8 waves per CU, the matrix cores busy a quarter
+// of the time.  32 slabs of 2048 cells, N = 64 (us, all launches): 326 in
+// chunks of 16 cells, 308 of 64 (one block per CU), 272 of 32.
 // Measured per correction against the eliminations' kernels (us): K = 200,
 // N = 8 17 (25); K = 2000, N = 64 48 (57); K = 2500, N = 64, 8 types 85
 // (153); K = 512, N = 64, 24 types 71 (310); 2000 cells of N = 64, no two
@@ -197,25 +199,43 @@ __device__ __forceinline__ void fpt_body(const FPTreeArgs &f, const int chunk) {
     // moment differences: the first loads go before the convergence gate
     // is resolved
     if constexpr (LEAF || UPDATE) {
-        const int n = nc * L2;
-        const bool sig = f.sigma != nullptr;
+        // two moments at a time: L2 is even (a caller's arrays are aligned to
+        // 8 bytes only, which a 16-byte load takes)
+        typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
+        const int n2 = nc * L2 / 2;
         const size_t g0 = (size_t)c0 * L2;
-        for (int base = 0; base < n; base += FPT_T * 4) {
-            double h[4], o[4], sg[4];
+        const d2u *half2 = reinterpret_cast<const d2u *>(f.half + g0), *old2 = reinterpret_cast<const d2u *>(f.old + g0);
+        auto moments = [&](auto &&scale) {
+            for (int base = 0; base < n2; base += FPT_T * 4) {
+                d2 h[4], o[4], sg[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const size_t g = g0 + min(base + tid + FPT_T * u, n - 1);
-                h[u] = f.half[g];
-                o[u] = f.old[g];
-                sg[u] = sig ? f.sigma[g] : 1.0;
-            }
-            if (base == 0 && skipped(f.skip)) return;
+                for (int u = 0; u < 4; ++u) {
+                    if (base + FPT_T * u >= n2) break;
+                    const int e = min(base + tid + FPT_T * u, n2 - 1);
+                    h[u] = half2[e];
+                    o[u] = old2[e];
+                    sg[u] = scale(e);
+                }
+                if (base == 0 && skipped(f.skip)) return false;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int e = base + tid + FPT_T * u;
-                const int r = (int)__umulhi((unsigned)e, f.rcpL2);
-                if (e < n) A[r * lda + e - r * L2] = sig ? (h[u] - o[u]) * sg[u] : h[u] - o[u];
+                for (int u = 0; u < 4; ++u) {
+                    if (base + FPT_T * u >= n2) break;
+                    const int e = base + tid + FPT_T * u;
+                    const int r = (int)__umulhi((unsigned)(2 * e), f.rcpL2);
+                    if (e < n2) {
+                        double *a = A + r * lda + 2 * e - r * L2;
+                        a[0] = (h[u].x - o[u].x) * sg[u].x;
+                        a[1] = (h[u].y - o[u].y) * sg[u].y;
+                    }
+                }
             }
+            return true;
+        };
+        if (f.sigma) {
+            const d2u *sigma2 = reinterpret_cast<const d2u *>(f.sigma + g0);
+            if (!moments([&](int e) -> d2 { return sigma2[e]; })) return;
+        } else {
+            if (!moments([&](int) { return d2{1.0, 1.0}; })) return;
         }
         if (l2p > L2)
             for (int i = tid; i < nc * (l2p - L2); i += FPT_T) A[(i / (l2p - L2)) * lda + L2 + i % (l2p - L2)] = 0.0;
