@@ -88,6 +88,11 @@ constexpr int kLongCells = 16384;
 // candidate segment lengths of the long-slab scan (the autotuner keeps the
 // fastest on the handle's own long slabs; 1024 without long slabs)
 constexpr int kSegCandidates[3] = {512, 1024, 2048};
+// wavefronts that the passes over the segments want in flight, and the most
+// parts that a segment is cut into for them.  One slab of 65536 cells and 256
+// angles (us, means over the three lengths): whole segments, at most 512
+// wavefronts, 88 for the maps and 120 for the sweep; in parts 34 and 55.
+constexpr int kSegWaves = 2048, kSegParts = 8;
 
 struct LongSeg {
     int slab, angle0, c0, c1;   // cells [c0, c1) of angles angle0 .. angle0+63

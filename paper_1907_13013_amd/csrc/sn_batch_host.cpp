@@ -405,16 +405,22 @@ sn_status batch_setup(const sn_problem_desc *d, hipStream_t st, BatchData **out,
         };
         {
             // long slabs: chains of (slab, 64-angle block) cut into segments
-            // of about len cells, one list per candidate length
+            // of about len cells, one list per candidate length; with few
+            // segments each is cut further, so that about kSegWaves wavefronts
+            // are in flight
             size_t max_segs = 0;
             for (int c = 0; c < 3; ++c) {
                 const int len = kSegCandidates[c];
+                long long waves = 0;
+                for (const BatchSlab &m : B->host_slabs)
+                    if (m.K >= kLongCells) waves += (long long)((m.K + len - 1) / len) * ((m.N + 63) / 64);
+                const int parts = waves ? (int)std::min<long long>(kSegParts, std::max<long long>(1, kSegWaves / waves)) : 1;
                 std::vector<LongSeg> segs;
                 std::vector<int> chain_first;
                 for (int b = 0; b < ns; ++b) {
                     const BatchSlab &m = B->host_slabs[b];
                     if (m.K < kLongCells) continue;
-                    const int nseg = (m.K + len - 1) / len;
+                    const int nseg = (m.K + len - 1) / len * parts;
                     for (int a0 = 0; a0 < m.N; a0 += 64) {
                         const int first = (int)segs.size();
                         chain_first.push_back(first);
