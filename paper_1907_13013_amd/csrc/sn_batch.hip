@@ -844,6 +844,9 @@ template <int W, typename PhiT>
 __global__ void src_batch_p(BatchSrcArgs g);  // persistent FP32 source GEMM (below)
 template <int W, typename PhiT>
 __global__ void src_batch_sp(BatchSrcArgs g);  // persistent split-BF16 source GEMM (below)
+__global__ void src_batch_p3(BatchSrcArgs g);  // W = 256 in BF16 pieces (below)
+__global__ void mom_batch_p3(BatchMomArgs g);
+extern const std::uint32_t kP3Lds;
 
 template <int W, typename PhiT>
 static void launch_src_wt(const BatchSrcArgs &a, bool split, hipStream_t s, KernelTimer *t) {
@@ -872,11 +875,17 @@ static void launch_src_w(const BatchSrcArgs &a, bool split, hipStream_t s, Kerne
     if constexpr (W <= 256) {
         // W = 16 classes run the 32-wide kernel (half its columns zero)
         constexpr int WP = W < 32 ? 32 : W;
+        // the solve's iterates at W = 256: BF16 pieces (186 / 154 us, see there)
+        if (W == 256 && a.pblocks_p3 > 0 && !split && a.phi32 && a.meta) {
+            LAUNCH(KID_SRC_BATCH, t, src_batch_p3, dim3((unsigned)a.pblocks_p3), dim3(512), kP3Lds, s, a);
+            return;
+        }
         if (a.pblocks > 0 && !split && a.meta) {
             const std::uint32_t lds = (std::uint32_t)(PUnit<WP>::ROWS * (WP + 4) * sizeof(float));
-            if (a.phi32)
-                LAUNCH(KID_SRC_BATCH, t, (src_batch_p<WP, float>), dim3((unsigned)a.pblocks), dim3(2 * WP), lds, s, a);
-            else
+            if (a.phi32) {
+                if constexpr (W < 256)
+                    LAUNCH(KID_SRC_BATCH, t, (src_batch_p<WP, float>), dim3((unsigned)a.pblocks), dim3(2 * WP), lds, s, a);
+            } else
                 LAUNCH(KID_SRC_BATCH, t, (src_batch_p<WP, double>), dim3((unsigned)a.pblocks), dim3(2 * WP), lds, s, a);
             return;
         }
@@ -1654,6 +1663,342 @@ __device__ __forceinline__ void pieces_product(const short *P, int r32, int lg, 
     }
 }
 
+// ---------------------------------------------------------------------------
+// W = 256 class GEMMs of the solve's FP32 iterates from BF16 pieces (six
+// products, as the fused passes' three pieces): persistent blocks of eight
+// waves over 32-row units as src_batch_p, wave w on columns 32 w .. 32 w +
+// 31.  B's first two pieces stay in registers (128 a lane); the third takes
+// part in one product of six and streams from L2, two or four steps of eight
+// k ahead (registers).  The next unit's operands are requested behind the last of that
+// stream, as loads return in order.  A's pieces alternate between two halves
+// of LDS, one barrier a unit, and the moments' test values are reduced once
+// per run of one slab's units.  FP32 MFMA bounded these: 110 us of the matrix
+// pipe for 131072 rows of 256 x 256, 186 us the source and 227 us the
+// moments.  The pieces take 41 us of it, and 154 and 152 us in all, with one
+// block a CU bound by the latency of a unit's stages.  Error against FP64
+// after six iterations, twelve slabs of 132 to 256 angles (mean of the
+// largest, relative): 8.3e-7 in FP32 products, 6.1e-7 in pieces.
+// ---------------------------------------------------------------------------
+constexpr int P3_W = 256, P3_KH = P3_W / 2, P3_NS8 = P3_KH / 8, P3_LDH = P3_W + 8;
+const std::uint32_t kP3Lds = 3 * 64 * P3_LDH * sizeof(short);
+
+struct P3Lane {
+    bf8 b[2][P3_NS8];
+    const bf8 *t2;
+    int stride;
+    __device__ __forceinline__ void load(const short4_t *const (&T)[3], int ncols, int c, int lg) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int st = 0; st < P3_NS8; ++st) b[q][st] = *at(T[q], ncols, c, lg, st);
+        t2 = at(T[2], ncols, c, lg, 0);
+        stride = ncols * 2;
+    }
+    __device__ static const bf8 *at(const short4_t *T, int ncols, int c, int lg, int st) {
+        const int k0 = lg * P3_KH + 8 * st;
+        return reinterpret_cast<const bf8 *>(&T[((k0 / 16) * ncols + c) * 4 + (k0 % 16) / 4]);
+    }
+    // group g of the third piece: steps G g ..
+    template <int G>
+    __device__ __forceinline__ void third(int g, bf8 (&v)[G]) const {
+#pragma unroll
+        for (int u = 0; u < G; ++u) {
+            const int st = G * g + u;
+            v[u] = t2[(st / 2) * stride + (st & 1)];
+        }
+    }
+};
+
+// x's three pieces to element o of the piece arrays
+template <int M>
+__device__ __forceinline__ void p3_store(short *P, int o, const float (&x)[M]) {
+    typedef short sv __attribute__((ext_vector_type(M)));
+    sv pc[3];
+#pragma unroll
+    for (int t = 0; t < M; ++t) {
+        float r = x[t];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            const unsigned short h = bf16_rne(r);
+            pc[q][t] = (short)h;
+            r -= bf16_to_f32(h);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) *reinterpret_cast<sv *>(&P[q * 64 * P3_LDH + o]) = pc[q];
+}
+
+// acc = the unit's rows (P: its half of LDS) x B; v0: the third piece's first
+// group, kept (a load for it would wait for the stores of the unit before);
+// between(): loads of the next unit
+template <int GS, class Between>
+__device__ __forceinline__ void p3_product(const short *P, int r32, int lg, const P3Lane &L, const bf8 (&v0)[GS],
+                                           f16v &acc, Between &&between) {
+    constexpr int NG = P3_NS8 / GS;
+    bf8 vc[GS];
+#pragma unroll
+    for (int u = 0; u < GS; ++u) vc[u] = v0[u];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+        bf8 v1[GS];
+        if (g + 1 < NG) L.third(g + 1, v1);
+        if (g == NG / 2) between();
+#pragma unroll
+        for (int u = 0; u < GS; ++u) {
+            const int st = GS * g + u;
+            bf8 a[3];
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                a[q] = *reinterpret_cast<const bf8 *>(&P[q * 64 * P3_LDH + r32 * P3_LDH + lg * P3_KH + 8 * st]);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2], L.b[0][st], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], L.b[1][st], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], vc[u], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], L.b[0][st], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], L.b[1][st], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], L.b[0][st], acc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int u = 0; u < GS; ++u) vc[u] = v1[u];
+    }
+}
+
+__global__ void __launch_bounds__(2 * P3_W) __attribute__((amdgpu_waves_per_eu(2, 2))) src_batch_p3(BatchSrcArgs g) {
+    extern __shared__ __attribute__((aligned(16))) short sm_p3[];
+    constexpr int W = P3_W, NT = 2 * W, UR = PUnit<W>::ROWS, NP = PUnit<W>::NP;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int r32 = lane & 31, lg = lane >> 5;
+    const int N = g.N, L1 = g.L1;
+    constexpr int Q = W / 4, CSTEP = NT / Q, CI = UR / 2 / CSTEP;  // as in src_batch_p
+    const float *ph = src_phi<float>(g);
+    const float *qe = g.q_ext ? g.q_ext : g.q;
+    const size_t emask = g.q_ext ? ~(size_t)0 : 0;
+    const bool active = wave * 32 < N;          // the wave's columns exist
+    const int col = wave * 32 + r32, colc = min(col, N - 1);
+    P3Lane B;
+    B.load(g.Mt3, N, colc, lg);
+    bf8 v0[2];
+    B.third(0, v0);
+    const int l4 = tid % Q, cg = tid / Q;
+    const bool lval = 4 * l4 < L1;
+    const int l4c = lval ? l4 : L1 / 4 - 1;
+    float4 pf0[CI], pf1[CI], ps[CI];  // phi rows 2c, 2c+1 and sigma_s row c
+    auto prefetch = [&](const TileMeta &m, int unit) {
+        const int c0 = (m.row0 + (unit % NP) * UR) / 2;
+#pragma unroll
+        for (int i = 0; i < CI; ++i) {
+            const long long cell = min(c0 + cg + CSTEP * i, m.K - 1);
+            const float4 *p = reinterpret_cast<const float4 *>(ph) + (size_t)m.phi4 + cell * (L1 / 2) + l4c;
+            pf0[i] = p[0];
+            pf1[i] = p[L1 / 4];
+            ps[i] = reinterpret_cast<const float4 *>(g.sigma_s + 4 * (size_t)m.ss4)[cell * m.ss_step + l4c];
+        }
+    };
+    const TileMeta *meta = g.meta;
+    const unsigned long long *prev = gate_prev(g.gate);
+    const int nunits = g.ntiles * NP, G = (int)gridDim.x;
+    if ((int)blockIdx.x >= nunits) return;
+    __shared__ TileMeta dring[4];
+    const uint2 *mq = reinterpret_cast<const uint2 *>(meta);
+    const int qtr = tid & 3;
+    auto unit_of = [&](int k) { return min((int)blockIdx.x + k * G, nunits - 1); };
+    auto desc = [&](int k) { return mq[4 * (unit_of(k) / NP) + qtr]; };  // quarter of descriptor k
+    {
+        const uint2 d0 = desc(0), d1 = desc(1);
+        if (tid < 4) {
+            reinterpret_cast<uint2 *>(&dring[0])[qtr] = d0;
+            reinterpret_cast<uint2 *>(&dring[1])[qtr] = d1;
+        }
+    }
+    uint2 dpend = desc(2);
+    __syncthreads();
+    unsigned long long gb;
+    {
+        const TileMeta m0 = dring[0];
+        prefetch(m0, unit_of(0));
+        gb = gate_bits(prev, meta, m0.slab);
+    }
+#pragma unroll 1
+    for (int k = 0;; ++k) {
+        const int unit = (int)blockIdx.x + k * G;
+        if (unit >= nunits) break;
+        short *P = sm_p3 + (k & 1) * 32 * P3_LDH;
+        if (tid < 4) reinterpret_cast<uint2 *>(&dring[(k + 2) & 3])[qtr] = dpend;
+#pragma unroll
+        for (int i = 0; i < CI; ++i) {
+            const int c = cg + CSTEP * i;
+            const float4 f0 = pf0[i], f1 = pf1[i], z = ps[i];
+            const float a0[4] = {lval ? f0.x * z.x : 0.f, lval ? f0.y * z.y : 0.f, lval ? f0.z * z.z : 0.f, lval ? f0.w * z.w : 0.f};
+            const float a1[4] = {lval ? f1.x * z.x : 0.f, lval ? f1.y * z.y : 0.f, lval ? f1.z * z.z : 0.f, lval ? f1.w * z.w : 0.f};
+            p3_store<4>(P, (2 * c) * P3_LDH + 4 * l4, a0);
+            p3_store<4>(P, (2 * c + 1) * P3_LDH + 4 * l4, a1);
+        }
+        __syncthreads();  // this half is staged, and every wave is done with the unit before
+        const TileMeta mc = dring[k & 3], mn = dring[(k + 1) & 3];
+        const int row0 = mc.row0 + (unit % NP) * UR;
+        const int rows = min(UR, 2 * mc.K - row0);  // <= 0: the part past a short tile
+        const bool skip = rows <= 0 || gate_done(prev, gb, g.gate.tol);
+        const bool work = active && !skip;
+        unsigned long long gbn = 0;
+        auto next = [&]() {
+            prefetch(mn, unit_of(k + 1));
+            dpend = desc(k + 3);
+            gbn = gate_bits(prev, meta, mn.slab);
+        };
+        if (work) {
+            float e[16];
+            f16v acc;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) acc[j] = 0.f;
+            p3_product(P, r32, lg, B, v0, acc, [&]() {
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    const int row = row0 + min(acc32_row(0, j, lg), rows - 1);
+                    e[j] = qe[(4 * (size_t)mc.psi4 + (size_t)row * N + colc) & emask];
+                }
+                next();
+            });
+            if (col < N) {
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    const int rl = acc32_row(0, j, lg);
+                    if (rl < rows) g.q[q_index_m(g, mc, row0 + rl, col)] = acc[j] + (g.q_ext ? e[j] : 0.0f);
+                }
+            }
+        } else {
+            next();
+        }
+        gb = gbn;
+    }
+}
+
+__global__ void __launch_bounds__(2 * P3_W) __attribute__((amdgpu_waves_per_eu(2, 2))) mom_batch_p3(BatchMomArgs g) {
+    extern __shared__ __attribute__((aligned(16))) short sm_p3[];
+    constexpr int W = P3_W, NT = 2 * W, UR = PUnit<W>::ROWS, NP = PUnit<W>::NP;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int r32 = lane & 31, lg = lane >> 5;
+    const int N = g.N, L1 = g.L1;
+    constexpr int PR = W / 2, CSTEP = NT / PR, CI = UR / 2 / CSTEP, NW = W / 32;  // as in mom_batch_p
+    float *out = MomIO<float>::out(g);
+    const float *refp = MomIO<float>::ref(g);
+    const bool stop = refp != nullptr;
+    const float *ref = stop ? refp : out;
+    const size_t emask = stop ? ~(size_t)0 : 0;
+    const bool active = wave * 32 < L1;
+    const int col = wave * 32 + r32, colc = min(col, L1 - 1);
+    P3Lane B;
+    B.load(g.Vt3, L1, colc, lg);
+    bf8 v0[4];
+    B.third(0, v0);
+    const int pi = tid % PR, cg = tid / PR;
+    const int n = 2 * pi;
+    const bool nval = n < N;
+    const int nc = nval ? n : N - 2;
+    const int dir = nc >= N / 2 ? 1 : 0;
+    const int a = nc - dir * (N / 2);
+    float4 pf[CI];
+    auto prefetch = [&](const TileMeta &m, int unit) {
+        const int c0 = (m.row0 + (unit % NP) * UR) / 2;
+        const float *base = g.psi + 4 * (size_t)m.psi4 + (long long)dir * m.K * N + 2 * a;
+#pragma unroll
+        for (int i = 0; i < CI; ++i) {
+            const long long cell = min(c0 + cg + CSTEP * i, m.K - 1);
+            pf[i] = *reinterpret_cast<const float4 *>(base + cell * N);
+        }
+    };
+    unsigned long long *slots = g.gate.iter ? g.gate.hist + hist_row(*g.gate.iter) * g.gate.ns : g.slot;
+    const TileMeta *meta = g.meta;
+    const unsigned long long *prev = gate_prev(g.gate);
+    const int nunits = g.ntiles * NP, G = (int)gridDim.x;
+    if ((int)blockIdx.x >= nunits) return;
+    __shared__ TileMeta dring[4];
+    const uint2 *mq = reinterpret_cast<const uint2 *>(meta);
+    const int qtr = tid & 3;
+    auto unit_of = [&](int k) { return min((int)blockIdx.x + k * G, nunits - 1); };
+    auto desc = [&](int k) { return mq[4 * (unit_of(k) / NP) + qtr]; };  // quarter of descriptor k
+    {
+        const uint2 d0 = desc(0), d1 = desc(1);
+        if (tid < 4) {
+            reinterpret_cast<uint2 *>(&dring[0])[qtr] = d0;
+            reinterpret_cast<uint2 *>(&dring[1])[qtr] = d1;
+        }
+    }
+    uint2 dpend = desc(2);
+    __syncthreads();
+    unsigned long long gb, dmax = 0ull;
+    {
+        const TileMeta m0 = dring[0];
+        prefetch(m0, unit_of(0));
+        gb = gate_bits(prev, meta, m0.slab);
+    }
+#pragma unroll 1
+    for (int k = 0;; ++k) {
+        const int unit = (int)blockIdx.x + k * G;
+        if (unit >= nunits) break;
+        short *P = sm_p3 + (k & 1) * 32 * P3_LDH;
+        if (tid < 4) reinterpret_cast<uint2 *>(&dring[(k + 2) & 3])[qtr] = dpend;
+#pragma unroll
+        for (int i = 0; i < CI; ++i) {
+            const int c = cg + CSTEP * i;
+            const float4 v = nval ? pf[i] : float4{0.f, 0.f, 0.f, 0.f};
+            // vector element 2 t + nd is (node nd, angle n + t)
+            const float x0[2] = {v.x, v.z}, x1[2] = {v.y, v.w};
+            p3_store<2>(P, (2 * c) * P3_LDH + n, x0);
+            p3_store<2>(P, (2 * c + 1) * P3_LDH + n, x1);
+        }
+        __syncthreads();  // this half is staged, and every wave is done with the unit before
+        const TileMeta mc = dring[k & 3], mn = dring[(k + 1) & 3];
+        const int row0 = mc.row0 + (unit % NP) * UR;
+        const int rows = min(UR, 2 * mc.K - row0);  // <= 0: the part past a short tile
+        const bool skip = rows <= 0 || gate_done(prev, gb, g.gate.tol);
+        const bool work = active && !skip;
+        unsigned long long gbn = 0;
+        auto next = [&]() {
+            prefetch(mn, unit_of(k + 1));
+            dpend = desc(k + 3);
+            gbn = gate_bits(prev, meta, mn.slab);
+        };
+        if (work) {
+            float e[16];
+            f16v acc;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) acc[j] = 0.f;
+            p3_product(P, r32, lg, B, v0, acc, [&]() {
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    const int row = row0 + min(acc32_row(0, j, lg), rows - 1);
+                    e[j] = ref[(4 * (size_t)mc.phi4 + (size_t)row * L1 + colc) & emask];
+                }
+                next();
+            });
+            if (col < L1) {
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    const int rl = acc32_row(0, j, lg);
+                    if (rl < rows) {
+                        const double v = (double)acc[j];
+                        out[4 * (size_t)mc.phi4 + (size_t)(row0 + rl) * L1 + col] = (float)v;
+                        if (stop) {
+                            const unsigned long long d =
+                                (unsigned long long)__double_as_longlong(fabs(v - (double)e[j]));
+                            dmax = d > dmax ? d : dmax;
+                        }
+                    }
+                }
+            }
+        } else {
+            next();
+        }
+        // the block's units of one slab share a reduction (a barrier each
+        // would line the waves up behind every unit's stores)
+        if (stop && (unit + G >= nunits || mn.slab != mc.slab)) {
+            __syncthreads();
+            slab_max_reduce_w<NW>(dmax, slots + mc.slab);
+            dmax = 0ull;
+        }
+        gb = gbn;
+    }
+}
+
 // waves per SIMD the register budget is sized for: three for the 128-wide
 // passes with three pieces (their 52 KB of LDS fit three blocks per CU) and
 // the apply passes from 64 wide (staged rows or the moments' B fragments
@@ -2069,14 +2414,16 @@ void launch_fused_iso(const BatchIsoArgs &a, hipStream_t s) {
 
 int persistent_gemm_blocks(int N, int L1, int kind, bool vec4, int ntiles) {
     const int w = std::max(32, class_width(N, L1));  // W = 16 classes run the 32-wide kernels
-    // W = 256: the sources only (the persistent moments kernel, one 32-row
-    // chain per wave there, measured slower than the tile-per-block one)
-    if (!vec4 || ntiles <= 0 || w > 256 || (kind == 1 && w > 128)) return 0;
+    // W = 256: kind 0 is the boundary calls' FP64 source, kind 3 both GEMMs
+    // of the solve in BF16 pieces; the boundary's moments take a block per tile
+    if (!vec4 || ntiles <= 0 || w > 256 || (kind == 1 && w > 128) || (kind == 3 && w != 256)) return 0;
     const bool mom = kind == 1;
     size_t lds = (size_t)(w == 256 ? PUnit<256>::ROWS : TM) * (w + 4) * sizeof(float);
     int per_cu = 0, dev = 0, cus = 0;
     hipError_t e = hipSuccess;
-    if (kind == 2) {
+    if (kind == 3) {
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, src_batch_p3, 512, kP3Lds);
+    } else if (kind == 2) {
         // split-BF16 source (the class tables are built at least 32 wide)
         lds = (size_t)2 * (w == 256 ? PUnit<256>::ROWS : TM) * (w + 4) * sizeof(short);
         e = w == 32    ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (src_batch_sp<32, float>), 64, lds)
@@ -2093,8 +2440,7 @@ int persistent_gemm_blocks(int N, int L1, int kind, bool vec4, int ntiles) {
         e = mom ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, mom_batch_p<128>, 256, lds)
                 : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (src_batch_p<128, float>), 256, lds);
     else
-        e = mom ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, mom_batch_p<256>, 512, lds)
-                : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (src_batch_p<256, float>), 512, lds);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (src_batch_p<256, double>), 512, lds);
     if (e != hipSuccess || per_cu <= 0 || hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) {
         (void)hipGetLastError();
@@ -2107,7 +2453,11 @@ int persistent_gemm_blocks(int N, int L1, int kind, bool vec4, int ntiles) {
 template <int W>
 static void launch_mom_w(const BatchMomArgs &a, hipStream_t s, KernelTimer *t) {
     const std::uint32_t lds = (std::uint32_t)(TM * (W + 4) * sizeof(float));
-    if constexpr (W <= 256) {
+    if (W == 256 && a.pblocks_p3 > 0 && a.phi32 && a.dirmajor && a.meta) {
+        LAUNCH(KID_MOM_BATCH, t, mom_batch_p3, dim3((unsigned)a.pblocks_p3), dim3(512), kP3Lds, s, a);
+        return;
+    }
+    if constexpr (W < 256) {
         constexpr int WP = W < 32 ? 32 : W;  // as in launch_src_w
         if (a.pblocks > 0 && a.phi32 && a.dirmajor && a.meta) {
             const std::uint32_t ldsp = (std::uint32_t)(PUnit<WP>::ROWS * (WP + 4) * sizeof(float));

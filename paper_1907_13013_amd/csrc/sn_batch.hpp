@@ -172,6 +172,9 @@ struct BatchSrcArgs {
     // persistent kernels read the tiles through meta ([ntiles])
     int pblocks = 0, pblocks_split = 0;
     const TileMeta *meta = nullptr;
+    // > 0: grid of the W = 256 kernel in BF16 pieces, and its table
+    int pblocks_p3 = 0;
+    const short4_t *Mt3[3] = {nullptr, nullptr, nullptr};
 };
 
 // phi = psi x Vt (FP32 MFMA, FP64 or FP32 out) over the tiles of one class,
@@ -195,6 +198,8 @@ struct BatchMomArgs {
     float *buf0 = nullptr, *buf1 = nullptr;
     int pblocks = 0;                       // as in BatchSrcArgs
     const TileMeta *meta = nullptr;
+    int pblocks_p3 = 0;
+    const short4_t *Vt3[3] = {nullptr, nullptr, nullptr};
 };
 
 // Fused source iteration (handles whose slabs all have at most

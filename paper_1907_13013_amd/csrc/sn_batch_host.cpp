@@ -305,6 +305,9 @@ sn_status batch_setup(const sn_problem_desc *d, hipStream_t st, BatchData **out,
                                                m.ab_off + 2 * (tm.row0 / (2 * kFusedCells)) * m.N, 0, 0});
                     }
                     c.ftiles = bupload(*B, ft, st);
+                }
+                c.pblocks_p3 = persistent_gemm_blocks(c.N, c.L1, 3, vec4, c.ntiles);
+                if (c.ftiles || c.pblocks_p3 > 0) {
                     const int w = std::max(32, class_width(c.N, c.L1));
                     std::vector<short4_t> pm[3], pv[3];
                     split3_tables(Mt_h[kv.second], c.N, c.L1, w, pm);
@@ -529,6 +532,8 @@ static void moments(BatchData &B, const float *psi, double *phi, const double *r
         g.buf0 = buf0; g.buf1 = buf1;
         g.dirmajor = dirmajor;
         g.pblocks = B.persistent_gemms ? c.pblocks_mom : 0;
+        g.pblocks_p3 = B.persistent_gemms ? c.pblocks_p3 : 0;
+        for (int q = 0; q < 3; ++q) g.Vt3[q] = c.Vt3[q];
         g.meta = c.meta;
         launch_mom_batch(g, st, t);
     }
@@ -547,6 +552,8 @@ static void source(BatchData &B, const double *phi, const float *phi32, const fl
         g.buf0 = buf0; g.buf1 = buf1;
         g.dirmajor = dirmajor;
         g.pblocks = B.persistent_gemms ? c.pblocks_src : 0;
+        g.pblocks_p3 = B.persistent_gemms ? c.pblocks_p3 : 0;
+        for (int q = 0; q < 3; ++q) g.Mt3[q] = c.Mt3[q];
         g.pblocks_split = B.persistent_gemms ? c.pblocks_split : 0;
         g.meta = c.meta;
         launch_src_batch(g, B.split_bf16, st, t);
