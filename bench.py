@@ -35,14 +35,14 @@ HBM_PEAK_GBS = 8000.0
 # to the value recorded in it
 TRAFFIC_SETS = {
     "fpsa": ("profiles/fpsa_wfd_srk_slab_2000_traffic.txt",
-             ("paper_1907_13013_amd/csrc/sn_kernels.hip", "paper_1907_13013_amd/csrc/sn_kernels.hpp")),
+             ("paper_1907_13013_amd/csrc/sn_kernels.hip", "paper_1907_13013_amd/csrc/sn_kernels.hpp",
+              "paper_1907_13013_amd/csrc/sn_fp_tree.hip", "paper_1907_13013_amd/csrc/sn_device.hpp")),
     "batch": ("profiles/batched_kernels_batch4096_traffic.txt",
               ("paper_1907_13013_amd/csrc/sn_batch.hip", "paper_1907_13013_amd/csrc/sn_batch.hpp")),
 }
 # kernels each counter summary covers
 SET_KERNELS = {
-    "fpsa": ("gemm_fp_source", "gemm_fp_update", "sweep_aggregate", "sweep_scan", "sweep_apply", "stopping_test",
-             "fp_matvec", "fp_chain", "fp_carry", "fp_fixup", "exit_flux"),
+    "fpsa": ("sweep_aggregate", "sweep_scan", "sweep_apply", "fp_tree_up", "fp_tree_update", "exit_flux"),
     "batch": ("sweep_batch_dm", "sweep_batch_f32", "src_batch_p<128>", "mom_batch_p<128>", "src_batch_p<64>",
               "mom_batch_p<64>", "src_batch_p<32>", "mom_batch_p<32>", "fused_scan",
               *(f"fused_{k}{s}<{w}>" for s in ("", "_sp") for w in (128, 64, 32) for k in ("aggregate", "apply"))),
@@ -51,15 +51,11 @@ SET_KERNELS = {
 # (the 32-wide kernels also run the N = 16 class)
 FUSED_LAUNCHES = {128: 1, 64: 1, 32: 2}
 # substrings of the rocprofv3 kernel names of the timed kernel identities
-# (the two GEMM instances of the correction are told apart by their K-chunk
-# count on the 2000-cell S_64 workload: <2> forms the Fokker-Planck source
-# from 2(L+1) = 128 moments, <3> the update from 128 moments and 64 inflows)
-ROCPROF_NAME = {"gemm_fp_source": "snfpsa::gemm_f64_mfma<2>", "gemm_fp_update": "snfpsa::gemm_f64_mfma<3>",
-                "sweep_aggregate": "snfpsa::sweep_aggregate",
-                "sweep_scan": "snfpsa::sweep_scan_carry", "sweep_apply": "snfpsa::sweep_apply",
-                "stopping_test": "snfpsa::stopping_test", "fp_matvec": "snfpsa::fp_matvec",
-                "fp_chain": "snfpsa::fp_chain", "fp_carry": "snfpsa::fp_carry",
-                "fp_fixup": "snfpsa::fp_fixup", "exit_flux": "snfpsa::exit_flux",
+# (the tree's launches differ in their mode bits: leaves 1, up 2, root 4,
+# down 8, update 16)
+ROCPROF_NAME = {"sweep_aggregate": "snfpsa::sweep_aggregate", "sweep_scan": "snfpsa::sweep_scan_carry",
+                "sweep_apply": "snfpsa::sweep_apply", "fp_tree_up": "snfpsa::fpt_kernel<3,",
+                "fp_tree_update": "snfpsa::fpt_kernel<24,", "exit_flux": "snfpsa::exit_flux",
                 "sweep_batch_dm": "snfpsa::sweep_batch_dm", "sweep_batch_f32": "snfpsa::sweep_batch_f32",
                 # persistent FP32 class GEMMs of the batched solve (<32> also runs the W = 16 classes)
                 "src_batch_p<128>": "snfpsa::src_batch_p<128, float>", "mom_batch_p<128>": "snfpsa::mom_batch_p<128>",
@@ -109,46 +105,28 @@ def read_traffic_summary(kernel: str, which: str = "fpsa"):
     return float(v) if v is not None else None
 
 
-def algorithmic_bytes_per_iteration(K, N, L1, P, fused_source=True):
+def algorithmic_bytes_per_iteration(K, N, L1):
     """Bytes each kernel must move per FPSA iteration (FP64), by kernel name,
     with the number of launches of that kernel per iteration.  The workload's
-    sweeps carry the scattering source and the moments (fused path), and,
-    the slab having one cell type, its correction's Fokker-Planck source is
-    formed inside fp_matvec (fused_source; otherwise by a gemm_f64_mfma
-    launch).
+    sweeps carry the scattering source and the moments (fused path); its
+    correction runs on the doubling tree.
 
     sweep_aggregate  phi and the external source in, the source q out (the
                      tile scan itself works on the tile in LDS)
     sweep_apply      q in, the half-step moments out
-    gemm_fp_source   gemm_f64_mfma forming the Fokker-Planck source:
-                     phi_half, phi_old in, s out
-    gemm_fp_update   gemm_f64_mfma forming the corrected moments: phi_half,
-                     phi_old and the interface inflow in, phi_new out
-    fp_matvec        per cell Hm and Hb, the source vector (fused: phi_half
-                     and phi_old instead), f and g written
-    fp_chain         per cell G and Gb, f and g read, the local values written
-    fp_carry         the chunk transfer products (P(P-1)/2 per direction)
-    fp_fixup         per cell PsiF, PsiB, W, W rho and sig, the local values
-                     read and the inflow written
-    The small tables every block reads (E, Mt, Vt) come from cache and are
-    not counted.
+    fp_tree_up       phi_half and phi_old in, the interfaces' zero-inflow
+                     values out
+    fp_tree_update   phi_half, phi_old and the interfaces in, phi_new out
+    The launches between (fp_tree_mid) work on the chunks' ends only, and the
+    matrices and tables every block reads come from cache: not counted.
     """
-    NH, b = N // 2, 8
-    M2 = NH * NH
-    out = {
+    b = 8
+    return {
         "sweep_aggregate": (b * (2 * K * L1 + 4 * K * N), 1),
         "sweep_apply": (b * (2 * K * N + 2 * K * L1), 1),
-        "gemm_fp_update": (b * (6 * K * L1 + K * N), 1),
-        "fp_chain": (K * b * (2 * M2 + 2 * N), 1),
-        "fp_carry": (b * M2 * P * (P - 1), 1),
-        "fp_fixup": (K * b * (5 * M2 + 2 * N), 1),
+        "fp_tree_up": (b * (4 * K * L1 + K * N), 1),
+        "fp_tree_update": (b * (6 * K * L1 + K * N), 1),
     }
-    if fused_source:
-        out["fp_matvec"] = (K * b * (2 * M2 + 4 * L1 + N), 1)
-    else:
-        out["gemm_fp_source"] = (b * (4 * K * L1 + K * N), 1)
-        out["fp_matvec"] = (K * b * (2 * M2 + 2 * N), 1)
-    return out
 
 
 def copy_probe(mib: int) -> int:
@@ -794,7 +772,7 @@ def main() -> int:
                     help="print the MFMA-activity summary from a rocprofv3 --pmc output directory and a "
                          "--kernel-trace --stats one of the same command")
     ap.add_argument("--mfma-kernels", nargs="*", default=["gemm_f64_tall", "src_batch_p<128", "mom_batch_p<128>",
-                                                           "src_batch_p<256", "src_batch_sp<256", "mom_batch<256>"])
+                                                           "src_batch_p3", "src_batch_sp<256", "mom_batch_p3"])
     ap.add_argument("--summarize-stats", metavar="STATS_DIR",
                     help="print the top kernels of a rocprofv3 --kernel-trace --stats output directory")
     ap.add_argument("--summary-top", type=int, default=16, help="kernels listed by --summarize-stats")
@@ -923,8 +901,7 @@ def main() -> int:
     torch.cuda.synchronize()
     kt = S.kernel_timing()
     S.set_kernel_timing(False)
-    fused_src = not kt.get("gemm_fp_source", (0, 0.0))[0]
-    per_iter = algorithmic_bytes_per_iteration(K, N, L1, S.slab_info(0)["nchunks"], fused_src)
+    per_iter = algorithmic_bytes_per_iteration(K, N, L1)
     # every kernel of the iteration against the HBM roofline, each GEMM
     # instance on its own; the dominant one (largest total time) is the line's
     # roofline

@@ -493,7 +493,7 @@ LaunchShape fpt_shape(const FPTreeArgs &f, int mode) {
     sh.gx = f.chunks;
     sh.block = FPT_T;
     const int m = kFptModes[mode];
-    sh.kid = (m & FPT_UPDATE) ? KID_GEMM_FP_UPDATE : ((m & FPT_LEAF) ? KID_FP_MATVEC : KID_FP_CARRY);
+    sh.kid = (m & FPT_UPDATE) ? KID_FP_TREE_UPDATE : ((m & FPT_LEAF) ? KID_FP_TREE_UP : KID_FP_TREE_MID);
     size_t d = (size_t)((m & FPT_ROOT) ? 2 : 1) * (f.rows + 1) * f.ldy;
     if (m & (FPT_LEAF | FPT_UPDATE)) d += (size_t)f.rows * f.lda;
     sh.lds = (unsigned)(d * sizeof(double));

@@ -30,7 +30,8 @@ const char *kernel_name(int id) {
                                            "exit_flux",     "sweep_batch_f32", "src_batch",
                                            "mom_batch",     "adjoint_aux",     "krylov",
                                            "gemm_fp_source", "gemm_fp_update", "fused_aggregate",
-                                           "fused_scan",    "fused_apply"};
+                                           "fused_scan",    "fused_apply",     "fp_tree_up",
+                                           "fp_tree_mid",   "fp_tree_update"};
     return (id >= 0 && id < KID_COUNT) ? names[id] : "";
 }
 

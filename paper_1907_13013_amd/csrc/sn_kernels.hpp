@@ -166,6 +166,9 @@ enum KernelId {
     KID_FUSED_AGG,        // batched fused iteration: aggregate pass
     KID_FUSED_SCAN,       // batched fused iteration: tile-map scan
     KID_FUSED_APPLY,      // batched fused iteration: apply pass with the moments
+    KID_FP_TREE_UP,
+    KID_FP_TREE_MID,
+    KID_FP_TREE_UPDATE,
     KID_COUNT
 };
 const char *kernel_name(int id);
