@@ -314,7 +314,11 @@ bool build_fp_factors_coef(int K, int N, int L, const double *h, const double *s
     if (chunk > K) chunk = K;
     out.chunk = chunk;
     out.nchunks = (K + chunk - 1) / chunk;
-    if (tree_slabs > 0 && build_fp_tree(K, N, L, tree_slabs, ct, out, out.tree)) return true;
+    if (tree_slabs > 0 && build_fp_tree(K, N, L, tree_slabs, ct, out, out.tree)) {
+        // all in out.tree.frag now
+        for (dvec *v : {&out.tree.mats, &out.EsrcT, &out.PhisrcT, &out.PhiinfT}) dvec().swap(*v);
+        return true;
+    }
     out.tree = FPTree();
 
     // ---- Riccati eliminations from both faces

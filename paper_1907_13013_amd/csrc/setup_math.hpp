@@ -161,8 +161,9 @@ bool build_fp_tree(int K, int N, int L, int slabs, const FPCellTypes &ct, const 
 // sigma_tr = sigma_s0 - sigma_s1.  Returns false if a cell block is
 // singular.  The FPSA residual's scattering matrix is folded into the
 // source maps (EsrcT, PhisrcT act on phi_half - phi_old).  With
-// tree_slabs > 0 (slabs solved together), a slab gets its doubling tree and the
-// cell maps instead of the eliminations' matrices (tree.stages is empty otherwise).
+// tree_slabs > 0 (slabs solved together), a slab gets its doubling tree,
+// whose frag holds all matrices and cell maps (the other arrays are given
+// back), instead of the eliminations' matrices (tree.stages is empty otherwise).
 bool build_fp_factors(int K, int N, int L, const double *h, const double *sigma_t,
                       const double *sigma_s, const dvec &mu, const dvec &w,
                       const dvec &A, FPFactors &out, int chunk_hint = 0,
