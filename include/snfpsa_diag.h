@@ -3,9 +3,9 @@
  *
  * These calls expose what sn_setup computes on the host (quadrature, angular
  * Laplacians, and the factorised Fokker-Planck operator) so that the setup
- * can be checked on a machine without a GPU.  They launch no device work
- * and no solver call uses them.  All arrays are host memory, FP64 unless
- * stated, row-major.
+ * can be checked on a machine without a GPU; the last one switches a kernel
+ * variant off, for tests.  They launch no device work and no solver call
+ * uses them.  All arrays are host memory, FP64 unless stated, row-major.
  */
 #ifndef SNFPSA_DIAG_H
 #define SNFPSA_DIAG_H
@@ -49,6 +49,13 @@ sn_status sn_diag_fp_info(sn_diag_fp p, int32_t *info);
  *       11 backward chunk transfer products ThB [nchunks(nchunks-1)/2][N/2][N/2] */
 sn_status sn_diag_fp_get(sn_diag_fp p, int32_t which, void *dst);
 sn_status sn_diag_fp_free(sn_diag_fp p);
+
+/* The 256-wide classes of a batched (SN_F32 / SN_BF16X3) handle run the
+ * solve's source and moments from BF16 pieces where the device can hold
+ * those kernels.  enable = 0 takes them as not held, so that the kernels
+ * that stand in for them can be tested; enable != 0 is the default.  Drops
+ * the handle's captured graphs.  SN_E_STATE for SN_F64 handles. */
+sn_status sn_diag_set_piece_gemms(sn_handle h, int32_t enable);
 
 #ifdef __cplusplus
 }

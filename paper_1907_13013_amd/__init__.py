@@ -43,7 +43,7 @@ EXPORTS = ["sn_setup", "sn_destroy", "sn_last_error", "sn_sweep", "sn_scatter_so
            "sn_set_kernel_timing",
            "sn_get_kernel_timing",
            "sn_diag_quadrature", "sn_diag_laplacian", "sn_diag_fp_factor", "sn_diag_fp_info",
-           "sn_diag_fp_get", "sn_diag_fp_free"]
+           "sn_diag_fp_get", "sn_diag_fp_free", "sn_diag_set_piece_gemms"]
 
 
 class SnError(RuntimeError):
@@ -109,6 +109,7 @@ def load_library():
     lib.sn_diag_fp_info.argtypes = [vp, vp]
     lib.sn_diag_fp_get.argtypes = [vp, i32, vp]
     lib.sn_diag_fp_free.argtypes = [vp]
+    lib.sn_diag_set_piece_gemms.argtypes = [vp, i32]
     for name in EXPORTS:
         if name not in ("sn_last_error",):
             getattr(lib, name).restype = C.c_int

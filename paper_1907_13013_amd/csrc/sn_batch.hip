@@ -880,14 +880,17 @@ static void launch_src_w(const BatchSrcArgs &a, bool split, hipStream_t s, Kerne
             LAUNCH(KID_SRC_BATCH, t, src_batch_p3, dim3((unsigned)a.pblocks_p3), dim3(512), kP3Lds, s, a);
             return;
         }
-        if (a.pblocks > 0 && !split && a.meta) {
-            const std::uint32_t lds = (std::uint32_t)(PUnit<WP>::ROWS * (WP + 4) * sizeof(float));
-            if (a.phi32) {
-                if constexpr (W < 256)
-                    LAUNCH(KID_SRC_BATCH, t, (src_batch_p<WP, float>), dim3((unsigned)a.pblocks), dim3(2 * WP), lds, s, a);
-            } else
-                LAUNCH(KID_SRC_BATCH, t, (src_batch_p<WP, double>), dim3((unsigned)a.pblocks), dim3(2 * WP), lds, s, a);
+        const std::uint32_t lds = (std::uint32_t)(PUnit<WP>::ROWS * (WP + 4) * sizeof(float));
+        if (a.pblocks > 0 && !split && !a.phi32 && a.meta) {
+            LAUNCH(KID_SRC_BATCH, t, (src_batch_p<WP, double>), dim3((unsigned)a.pblocks), dim3(2 * WP), lds, s, a);
             return;
+        }
+        // (iterates at W = 256 without room for the pieces: a block per tile, below)
+        if constexpr (W < 256) {
+            if (a.pblocks > 0 && !split && a.phi32 && a.meta) {
+                LAUNCH(KID_SRC_BATCH, t, (src_batch_p<WP, float>), dim3((unsigned)a.pblocks), dim3(2 * WP), lds, s, a);
+                return;
+            }
         }
     }
     if (a.phi32)

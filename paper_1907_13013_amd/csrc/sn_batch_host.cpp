@@ -532,7 +532,7 @@ static void moments(BatchData &B, const float *psi, double *phi, const double *r
         g.buf0 = buf0; g.buf1 = buf1;
         g.dirmajor = dirmajor;
         g.pblocks = B.persistent_gemms ? c.pblocks_mom : 0;
-        g.pblocks_p3 = B.persistent_gemms ? c.pblocks_p3 : 0;
+        g.pblocks_p3 = B.persistent_gemms && B.piece_gemms ? c.pblocks_p3 : 0;
         for (int q = 0; q < 3; ++q) g.Vt3[q] = c.Vt3[q];
         g.meta = c.meta;
         launch_mom_batch(g, st, t);
@@ -552,7 +552,7 @@ static void source(BatchData &B, const double *phi, const float *phi32, const fl
         g.buf0 = buf0; g.buf1 = buf1;
         g.dirmajor = dirmajor;
         g.pblocks = B.persistent_gemms ? c.pblocks_src : 0;
-        g.pblocks_p3 = B.persistent_gemms ? c.pblocks_p3 : 0;
+        g.pblocks_p3 = B.persistent_gemms && B.piece_gemms ? c.pblocks_p3 : 0;
         for (int q = 0; q < 3; ++q) g.Mt3[q] = c.Mt3[q];
         g.pblocks_split = B.persistent_gemms ? c.pblocks_split : 0;
         g.meta = c.meta;

@@ -59,6 +59,7 @@ struct BatchData {
     };
     bool use_graphs = true;
     bool persistent_gemms = true;          // persistent FP32 class GEMMs where eligible
+    bool piece_gemms = true;               // 256-wide classes: the GEMMs in BF16 pieces where eligible
     int *iter_dev = nullptr;
     hipStream_t gstream = nullptr;
     hipEvent_t gev = nullptr;

@@ -2589,6 +2589,16 @@ sn_status sn_get_kernel_timing(sn_handle h, int32_t kernel_id, const char **name
 // ---------------------------------------------------------------------------
 // Host diagnostics (snfpsa_diag.h): setup math only, no device work.
 // ---------------------------------------------------------------------------
+sn_status sn_diag_set_piece_gemms(sn_handle h, int32_t enable) {
+    sn_status cs = check_handle(h);
+    if (cs != SN_OK) return cs;
+    if (!h->batch) return fail(SN_E_STATE, "sn_diag_set_piece_gemms needs an SN_F32 or SN_BF16X3 handle");
+    h->batch->piece_gemms = enable != 0;
+    for (BatchData::GraphEntry &g : h->batch->graphs) (void)hipGraphExecDestroy(g.exec);
+    h->batch->graphs.clear();
+    return SN_OK;
+}
+
 sn_status sn_diag_quadrature(int32_t N, double *mu, double *w) {
     if (N < 1 || !mu || !w) return fail(SN_E_INVALID, "bad arguments");
     dvec m, ww;
