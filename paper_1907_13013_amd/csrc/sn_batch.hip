@@ -537,11 +537,9 @@ void launch_sweep_long(const BatchLongArgs &a, hipStream_t s, KernelTimer *t) {
 // layouts: lane l supplies A[l%16][k(l)] and B[k(l)][l%16]; accumulator
 // element r of lane l is D[4 (l/16) + r][l%16].
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ unsigned short bf16_rne(float x) {
-    unsigned int u = __float_as_uint(x);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (unsigned short)(u >> 16);
-}
+// x to the nearest BF16 number, ties to even (v_cvt_pk_bf16_f32, which keeps a
+// NaN of any bits a NaN)
+__device__ __forceinline__ unsigned short bf16_rne(float x) { return __builtin_bit_cast(unsigned short, (__bf16)x); }
 __device__ __forceinline__ float bf16_to_f32(unsigned short h) { return __uint_as_float((unsigned int)h << 16); }
 
 constexpr int TM = 64;
