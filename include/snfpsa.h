@@ -414,13 +414,17 @@ sn_status sn_set_graph_replay(sn_handle h, int32_t enable);
  * sn_solve and sn_solve_adjoint (SN_SI, SN_FPSA) on an SN_F64 handle with
  * two or more slabs run every kernel of an iteration as one launch per
  * kernel variant over all slabs (and cell-type segments), each slab with its
- * own workspace, iterates and stopping test, skipped by every launch after
- * its test has passed; slabs that share Fokker-Planck factors
- * (SN_FP_MEAN) have their blocks side by side so that the shared factors
- * are read from cache.  The results are those of the slab-by-slab solve:
- * the same iteration counts, with moments that agree to FP64 rounding (the
+ * own workspace, iterates and stopping test; slabs that share Fokker-Planck
+ * factors (SN_FP_MEAN) have their blocks side by side so that the shared
+ * factors are read from cache.  iters and resid_hist are those of the
+ * slab-by-slab solve: every iterate agrees with it to FP64 rounding (the
  * same kernels, whose batched instances the compiler may contract
- * differently; measured within 1e-11 of the largest moment).
+ * differently; measured within 1e-11 of the largest moment).  The slabs
+ * iterate together, though, until the slowest has passed its test and the
+ * iterations queued with that one are done: phi and psi_exit are of the last
+ * iteration run, which for a slab may be past iters[b] and so closer to its
+ * solution than the slab-by-slab solve's, by what that one had still to go
+ * (of the order of tol).
  * With kernel timing off, one iteration is captured into a HIP graph (once
  * per source, method and boundary mode, four kept per handle) and replayed
  * on a stream the handle owns, ordered after and before the caller's stream

@@ -170,8 +170,9 @@ constexpr int kSlots = 8;
 // handle (each slab and cell-type segment one descriptor, see MultiLaunch),
 // so an iteration of hundreds of slabs costs a dozen launches instead of a
 // dozen per slab.  Each slab keeps its own workspace, iterates, and column
-// of a stopping-test ring; a slab whose test has passed is skipped by every
-// later launch.  The launches read the iteration number from a device
+// of a stopping-test ring; all iterate until the slowest has passed its test
+// (one whose iterate no longer changes, or is not finite, is skipped by the
+// later launches).  The launches read the iteration number from a device
 // counter (advanced by the last launch of the iteration), so one set of
 // descriptors serves the whole solve.  Blocks are interleaved across slabs,
 // with slabs that share Fokker-Planck factors next to each other, so a
@@ -184,7 +185,6 @@ struct F64Plan {
     const void *qext = nullptr;
     bool bc = true;
     const unsigned long long *hist = nullptr;
-    double tol = 0.0;     // grouped Fokker-Planck launches test their slabs' convergence
     std::vector<MultiLaunch> launches;
     void *dev = nullptr;   // every launch's descriptors and block table (one allocation)
     void *dev2 = nullptr;  // the grouped launches' per-slab vector tables
@@ -744,26 +744,17 @@ static void plan_group(const std::vector<const PlanItem *> &items, const A PlanI
     out.push_back(L);
 }
 
-// A slab of a batched solve stops iterating once its test value is at most
-// this share of tol.  Its iterations until the slowest slab passes tol used
-// to run in full (a share of 0); the share keeps most of the digits that
-// they added beyond tol.
-constexpr double kBatchGate = 1.0 / 64;
-
-static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool problem_bc, double tol,
-                          F64Plan **out) {
+static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool problem_bc, F64Plan **out) {
     F64Batch &B = *h->f64b;
     for (size_t e = 0; e < B.plans.size(); ++e) {
         const F64Plan &p = B.plans[e];
-        if (p.method == method && p.qext == q_ext && p.bc == problem_bc && p.hist == h->hist && p.tol == tol) {
+        if (p.method == method && p.qext == q_ext && p.bc == problem_bc && p.hist == h->hist) {
             std::rotate(B.plans.begin() + e, B.plans.begin() + e + 1, B.plans.end());
             *out = &B.plans.back();
             return SN_OK;
         }
     }
     const int ns = (int)h->slabs.size();
-    SkipTest gate;  // prev is the iteration's (PATCH_SKIP)
-    gate.tol = tol * kBatchGate;
     // slabs sharing one factorisation (same factor arrays and sizes; padded
     // half-width <= 64) run their recurrences as groups of at most
     // kFPGroupMax slabs
@@ -816,7 +807,7 @@ static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool pro
         if (!fuse) {
             PlanItem it;
             it.kind = 0;
-            it.g = scatter_args(b, cur, qe, W.q, gate);
+            it.g = scatter_args(b, cur, qe, W.q);
             it.sh = gemm_shape(it.g);
             it.p = base;
             it.p.flags |= PATCH_A1_CUR;
@@ -824,7 +815,7 @@ static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool pro
             add(PH_SCATTER, it);
         }
         {
-            SweepArgs a = sweep_args(W, b, W.q, W.psi, problem_bc, gate);
+            SweepArgs a = sweep_args(W, b, W.q, W.psi, problem_bc);
             PlanItem it;
             it.kind = 1;
             it.p = base;
@@ -856,12 +847,12 @@ static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool pro
             it.kind = 0;
             it.p = base;
             if (method == SN_FPSA) {
-                it.g = moments_args(b, W.psi, W.phi_half, gate);
+                it.g = moments_args(b, W.psi, W.phi_half);
             } else {
                 FusedStop fs;
                 fs.ref = cur;
                 fs.slot = slot;
-                it.g = moments_args(b, W.psi, nxt, gate, &fs);
+                it.g = moments_args(b, W.psi, nxt, SkipTest(), &fs);
                 it.p.flags |= PATCH_C_NXT | PATCH_STOP;
             }
             it.sh = gemm_shape(it.g);
@@ -873,7 +864,7 @@ static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool pro
             FusedStop fs;
             fs.ref = cur;
             fs.slot = slot;
-            for (const TreeLaunch &tl : tree_launches(W, b, W.phi_half, cur, nxt, gate, &fs)) {
+            for (const TreeLaunch &tl : tree_launches(W, b, W.phi_half, cur, nxt, SkipTest(), &fs)) {
                 PlanItem it;
                 it.kind = 5;
                 it.t = tl.a;
@@ -889,7 +880,7 @@ static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool pro
         for (size_t sg = 0; sg + 1 < b.seg_begin.size(); ++sg) {
             PlanItem it;
             it.kind = 0;
-            it.g = fp_source_args(W, b, W.phi_half, cur, sg, gate);
+            it.g = fp_source_args(W, b, W.phi_half, cur, sg, SkipTest());
             it.sh = gemm_shape(it.g);
             it.p = base;
             it.p.flags |= PATCH_A1SUB_CUR;
@@ -900,7 +891,7 @@ static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool pro
         if (group_of[bi] < 0) {
             PlanItem it;
             it.kind = 2;
-            it.f = fp_args(W, b, gate);
+            it.f = fp_args(W, b, SkipTest());
             it.p = base;
             it.order = (uintptr_t)b.cellmats;  // slabs sharing factors side by side
             LaunchShape sh[4];
@@ -915,10 +906,10 @@ static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool pro
             const std::vector<int> &grp = groups[group_of[bi]];
             PlanItem it;
             it.kind = 4;
-            it.fg.f = fp_args(W, b, gate);
+            it.fg.f = fp_args(W, b, SkipTest());
             it.fg.nslab = (int)grp.size();
             it.fg.hist_stride = ns;
-            it.fg.tol = gate.tol;
+            it.fg.tol = 0.0;  // as the other launches: a slab iterates until the slowest has passed
             it.vec_off = vecs.size();
             for (int sb : grp) {
                 const Workspace &V = B.ws[sb];
@@ -945,7 +936,7 @@ static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool pro
             fs.slot = slot;
             PlanItem it;
             it.kind = 0;
-            it.g = fp_update_args(W, b, W.phi_half, cur, nxt, sg, gate, &fs);
+            it.g = fp_update_args(W, b, W.phi_half, cur, nxt, sg, SkipTest(), &fs);
             it.sh = gemm_shape(it.g);
             it.p = base;
             it.p.flags |= PATCH_A1SUB_CUR | PATCH_C_NXT | (single ? PATCH_STOP : 0u);
@@ -960,7 +951,6 @@ static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool pro
             it.st.b = cur;
             it.st.n = nphi;
             it.st.slot = slot;
-            it.st.skip = gate;
             it.sh = stop_shape(nphi);
             it.p = base;
             it.p.flags |= PATCH_STOPTEST;
@@ -974,7 +964,6 @@ static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool pro
     plan.qext = q_ext;
     plan.bc = problem_bc;
     plan.hist = h->hist;
-    plan.tol = tol;
     if (!vecs.empty()) {
         if (hipMalloc(&plan.dev2, vecs.size() * sizeof(FPSlabVecs)) != hipSuccess) {
             (void)hipGetLastError();
@@ -1053,7 +1042,12 @@ static sn_status f64_plan(sn_handle h, int method, const double *q_ext, bool pro
 }
 
 // SI / FPSA of every slab of a multi-slab FP64 handle in batched launches;
-// same arguments and results as the slab-by-slab path of solve_impl.
+// same arguments, iteration counts and histories as the slab-by-slab path of
+// solve_impl.  The slabs iterate together until the slowest has passed its
+// test, and to the end of the iterations queued with that one: phi and
+// psi_exit are of the last iteration run, past the slab's own iters.  (Slabs
+// stopped at a 64th of tol instead took 16 slabs of N = 16 to 64 from 8.5e-13
+// to 7.2e-11 off the converged moments at tol = 1e-8.)
 static sn_status solve_batched_f64(sn_handle h, int32_t method, double tol, int32_t max_iter, const double *q_ext,
                                    double *phi, double *psi_exit, int32_t *iters, double *resid_hist,
                                    hipStream_t st, bool problem_bc) {
@@ -1065,13 +1059,10 @@ static sn_status solve_batched_f64(sn_handle h, int32_t method, double tol, int3
     } catch (const HipError &e) {
         return fail(SN_E_HIP, std::string("HIP error in ") + e.where + ": " + hipGetErrorString(e.e));
     }
-    sn_status ps = f64_plan(h, method, q_ext, problem_bc, tol, &plan);
+    sn_status ps = f64_plan(h, method, q_ext, problem_bc, &plan);
     if (ps != SN_OK) return ps;
-    // its: iterations until the test passed; last: the slab's last executed
-    // iteration (0: none stopped it yet), whose iterate is the result
-    std::vector<int> its(ns, 0), last(ns, 0);
+    std::vector<int> its(ns, 0);
     std::vector<char> bad(ns, 0);
-    const double gate = tol * kBatchGate;
     try {
         HIPCHK(hipMemcpyAsync(B.phiA, phi, (size_t)h->phi_len * sizeof(double), hipMemcpyDeviceToDevice, st));
         static const int one = 1;
@@ -1130,35 +1121,22 @@ static sn_status solve_batched_f64(sn_handle h, int32_t method, double tol, int3
                                       (size_t)c * ns * sizeof(unsigned long long), hipMemcpyDeviceToHost, rs));
             });
             HIPCHK(hipStreamSynchronize(rs));
-            // iterations that the slowest slab needs to reach the gate, from
-            // its recent contraction rate
-            double need = 0.0;
             for (int b = 0; b < ns; ++b) {
-                auto value = [&](int m) {
-                    double v;
-                    std::memcpy(&v, &h->hist_host[hist_row(m) * ns + b], sizeof(double));
-                    return v;
-                };
-                for (int m = launched + 1; m <= launched + nb && !last[b]; ++m) {
-                    const double v = value(m);
-                    if (!its[b]) {
-                        if (resid_hist) resid_hist[(size_t)b * max_iter + m - 1] = v;
-                        if (passes(v)) {
-                            its[b] = m;
-                            bad[b] = !std::isfinite(v);
-                            --remaining;
-                        }
-                    }
-                    if (v <= gate || !std::isfinite(v)) last[b] = m;
-                }
                 if (its[b]) continue;
-                const int m = launched + nb, d = std::min(nb - 1, 8);
-                const double v = value(m), rho = d > 0 ? std::pow(v / value(m - d), 1.0 / d) : 1.0;
-                need = std::max(need, rho > 0.0 && rho < 1.0 && gate > 0.0 ? std::log(gate / v) / std::log(rho) + 1.0
-                                                                            : (double)kHistBatch);
+                for (int i = 0; i < nb; ++i) {
+                    double v;
+                    std::memcpy(&v, &h->hist_host[hist_row(launched + i + 1) * ns + b], sizeof(double));
+                    if (resid_hist) resid_hist[(size_t)b * max_iter + launched + i] = v;
+                    if (passes(v)) {
+                        its[b] = launched + i + 1;
+                        bad[b] = !std::isfinite(v);
+                        --remaining;
+                        break;
+                    }
+                }
             }
             launched += nb;
-            batch = (int)std::min(std::ceil(need), (double)std::min(2 * batch, kHistBatch));
+            batch = std::min(2 * batch, kHistBatch);
         }
         if (rs != st) {
             HIPCHK(hipEventRecord(B.gev, rs));
@@ -1173,7 +1151,7 @@ static sn_status solve_batched_f64(sn_handle h, int32_t method, double tol, int3
                 result = SN_NOT_CONVERGED;
             }
             iters[b] = its[b];
-            const double *fin = ((last[b] ? last[b] : launched) & 1) ? W.phiB : W.phiA;
+            const double *fin = (launched & 1) ? W.phiB : W.phiA;  // the iterate that psi_exit is of
             HIPCHK(hipMemcpyAsync(phi + sl.phi_off, fin, (size_t)sl.K * 2 * sl.L1 * sizeof(double),
                                   hipMemcpyDeviceToDevice, st));
             if (psi_exit)
