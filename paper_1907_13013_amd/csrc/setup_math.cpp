@@ -447,15 +447,14 @@ bool build_fp_factors_coef(int K, int N, int L, const double *h, const double *s
 // Doubling tree (see FPTree)
 // ---------------------------------------------------------------------------
 
-int fp_tree_nb(int N) {
-    int best = 2, pad = 0;
-    for (int nb = 2; nb <= 8; nb *= 2) {
-        const int p = (N + 4 * nb - 1) / (4 * nb) * (4 * nb);
-        if (nb == 2) pad = p;
-        if (p <= pad + pad / 7) best = nb;
-    }
-    return best;
-}
+// A wave waits for one batch of right operands while the next travels, so a
+// product of few rows is as long as its batches are many, and padding to whole
+// batches costs less than shorter ones.  us a correction in batches of 2, 4
+// and 8: K = 300, one type, N = 10 24.0 / 21.7 / 23.4, N = 20 28.1 / 26.3 /
+// 25.0, N = 34 39.4 / 34.8 / 35.5, N = 72 78 / 59 / 54, N = 104 108 / 84 / 77,
+// N = 130 317 / 186 / 132; 32 slabs of 500 cells, an iteration, N = 20 105 /
+// 100 / 101, N = 72 334 / 296 / 291, N = 104 516 / 447 / 438.
+int fp_tree_nb(int N) { return N <= 8 ? 2 : N <= 16 ? 4 : 8; }
 size_t fp_tree_ld(int N, int cols) {
     const int kb = 4 * fp_tree_nb(N);
     return (size_t)(cols + kb - 1) / kb * kb + 1;
