@@ -447,6 +447,69 @@ bool build_fp_factors_coef(int K, int N, int L, const double *h, const double *s
 // Doubling tree (see FPTree)
 // ---------------------------------------------------------------------------
 
+// A slab alone.  The eliminations take one source and one update launch a run
+// on all CUs, a level of the tree is one CU's stream of matrices: few runs and
+// cells, past 96 angles (where a level's stream is as long as 128's) and at
+// most 128 (past it the eliminations' chains leave LDS).  us an iteration,
+// eliminations / tree (two and three runs: means over three cuts):
+//   K                   100        150        240        400        640        760
+//   N = 104, 1 run    97 / 88   100 / 96  102 / 104  111 / 111  118 / 118  121 / 132
+//            2       118 / 122 120 / 123  122 / 129  131 / 141  143 / 146  150 / 149
+//   N = 116, 1        97 / 99  101 / 102  103 / 108  112 / 116  120 / 122  125 / 128
+//            2       118 / 129 120 / 132  122 / 136  131 / 149  146 / 152  153 / 149
+//            3       139 / 131 142 / 137  145 / 142  153 / 156  167 / 166  174 / 161
+//   N = 128, 1        91 / 98   93 / 101   96 / 108  104 / 115  111 / 120  127 / 126
+//            2       111 / 128 113 / 132  115 / 135  121 / 147  134 / 149  150 / 147
+//            3       132 / 131 134 / 134  135 / 139  143 / 155  160 / 165  173 / 159
+// K = 64, N = 128, 1 to 3 runs 91 / 75, 111 / 111, 131 / 113; N = 96, K = 240,
+// two runs 116 / 106; N = 130, K = 240, two runs 222 / 178.
+//
+// Slabs together.  A run costs the eliminations no launch then (one for all
+// slabs), but they move nine N/2 x N/2 matrices a cell, and slabs of which
+// some keep them and some take the tree would run one after the other: all of
+// a handle or none, of one padded half-width (one launch).  us an iteration:
+//   slabs x K           2 x 70    2 x 200    2 x 500    4 x 70    4 x 200    8 x 70    8 x 200
+//   N = 64, 1 run     65 / 57    77 / 62    84 / 88    72 / 58   79 / 63    79 / 61  100 / 77
+//           2         69 / 65    80 / 72    86 / 88    78 / 71   82 / 74    82 / 83  103 / 93
+//           4         70 / 74    79 / 107   87 / 96    78 / 78   83 / 114   82 / 87  102 / 106
+//           8         69 / 81    79 / 89    86 / 107   78 / 85   83 / 94    82 / 99  105 / 129
+//   N = 96, 1        106 / 82   117 / 125  145 / 125  107 / 84  132 / 131  118 / 104 225 / 146
+//           2        108 / 116  120 / 122  147 / 151  111 / 128 133 / 138  122 / 136 235 / 164
+//           4        108 / 136  120 / 136  147 / 152  110 / 142 134 / 137  122 / 162 237 / 156
+//   N = 128, 1       103 / 112  112 / 123  170 / 152  104 / 139 146 / 125  134 / 153 250 / 154
+//            2       105 / 164  114 / 154  174 / 180  107 / 168 150 / 173  140 / 184 256 / 184
+//            8       107 / 144  116 / 165  180 / 207  109 / 147 159 / 178  151 / 155 272 / 281
+// N = 48 with 4 runs 77 / 68 (2 x 70) to 92 / 83 (4 x 200); N = 144 with 2
+// runs 190 / 187 (2 x 70).  Past eight runs nothing was measured.
+bool fp_keeps_eliminations(const std::vector<FPSlabShape> &slabs) {
+    if (slabs.empty()) return false;
+    const bool wide = slabs[0].N > 64;
+    long long cells = 0;
+    int runs = 0, least = slabs[0].N;
+    for (const FPSlabShape &s : slabs) {
+        if (s.N <= 48 || s.N > 128 || (s.N > 64) != wide) return false;
+        cells += s.K;
+        runs = std::max(runs, s.runs);
+        least = std::min(least, s.N);
+    }
+    if (slabs.size() == 1) {
+        const int past = runs == 1 ? 104 : runs == 2 ? 96 : 124;
+        return runs <= 3 && least > past && cells > 64 && cells <= 700;
+    }
+    if (runs > 8) return false;
+    if (!wide) return runs >= 4 && cells <= 1600;
+    return runs == 1 ? least > 104 && cells <= 600 : cells <= 1000;
+}
+
+int fp_runs(int K, int L1, const double *h, const double *sigma_t, const double *sigma_s) {
+    int runs = 1;
+    for (int j = 1; j < K; ++j)
+        if (h[j] != h[j - 1] || (sigma_t && sigma_t[j] != sigma_t[j - 1]) ||
+            (sigma_s && !std::equal(sigma_s + (size_t)j * L1, sigma_s + (size_t)(j + 1) * L1, sigma_s + (size_t)(j - 1) * L1)))
+            ++runs;
+    return runs;
+}
+
 // A wave waits for one batch of right operands while the next travels, so a
 // product of few rows is as long as its batches are many, and padding to whole
 // batches costs less than shorter ones.  us a correction in batches of 2, 4
@@ -659,15 +722,6 @@ bool build_fp_tree(int K, int N, int L, int slabs, const FPCellTypes &ct, const 
     const size_t M2 = (size_t)NH * NH, N2 = (size_t)N * N;
     out = FPTree();
     const int ntypes = (int)ct.T.size();
-    // Widths up to 128 past 96 and few types: the eliminations, one launch a
-    // type on all CUs where a level here is one CU's stream of matrices.
-    // us a correction, eliminations / tree, N = 128: K = 240 with 1, 2, 3, 4
-    // and 6 types 69 / 78, 84 / 112, 106 / 108, 127 / 107, 168 / 114; one type
-    // and K = 40, 120, 500, 700, 1000 62 / 47, 66 / 78, 78 / 96, 87 / 100,
-    // 120 / 106.  Elsewhere the tree: K = 240, N = 112, 160 and 192 76 / 74,
-    // 222 / 133 and 252 / 163; K = 2000, N = 64 57 / 48; K = 2000, N = 64 and
-    // 200, 700, 2000 types 2510 / 97, 9000 / 146, 25000 / 197.
-    if (N > 112 && N <= 128 && ntypes <= 3 && K > 64 && K < 900) return false;
     // node classes: operators (T, R, R', T') per class, classes of equal
     // child pairs shared
     struct Node {

@@ -153,7 +153,17 @@ struct FPFactors {
     FPTree tree;
 };
 
-// false: use the eliminations (better there, a singular pair, or no cut fits).
+// A slab of a handle for the choice between the two: cells, angles, and runs
+// of equal cells (fp_runs; slab-mean coefficients: of equal widths, sigma_t
+// and sigma_s null).
+struct FPSlabShape {
+    int K, N, runs;
+};
+int fp_runs(int K, int L1, const double *h, const double *sigma_t, const double *sigma_s);
+// Whether the slabs of a handle keep the eliminations (tree_slabs = 0 below).
+bool fp_keeps_eliminations(const std::vector<FPSlabShape> &slabs);
+
+// false: use the eliminations (a singular pair, or no cut fits).
 // maps: the cell maps of the types (FPFactors::EsrcT, PhisrcT, PhiinfT).
 bool build_fp_tree(int K, int N, int L, int slabs, const FPCellTypes &ct, const FPFactors &maps, FPTree &out);
 

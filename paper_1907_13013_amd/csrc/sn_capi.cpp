@@ -1313,6 +1313,21 @@ sn_status sn_setup(const sn_problem_desc *d, void *stream, sn_handle *out) {
             *out = H;
             return SN_OK;
         }
+        // doubling trees for all slabs, or eliminations for all
+        int tree_slabs = 0;
+        if (H->has_fp) {
+            const bool mean = d->fp_coefficients == SN_FP_MEAN;
+            std::vector<FPSlabShape> shapes;
+            int64_t c0 = 0, s0 = 0;
+            for (int bi = 0; bi < d->num_slabs; ++bi) {
+                const int K = d->K[bi], L1 = d->L[bi] + 1;
+                shapes.push_back({K, d->N[bi], fp_runs(K, L1, d->h + c0, mean ? nullptr : d->sigma_t + c0,
+                                                       mean ? nullptr : d->sigma_s + s0)});
+                c0 += K;
+                s0 += (int64_t)K * L1;
+            }
+            if (!fp_keeps_eliminations(shapes)) tree_slabs = d->num_slabs;
+        }
         // SN_FP_MEAN: per slab the width-weighted means of sigma_a and
         // sigma_tr, rounded to two significant digits; slabs with equal
         // (K, N, L, widths, rounded means) share one factorisation.  The
@@ -1359,7 +1374,7 @@ sn_status sn_setup(const sn_problem_desc *d, void *stream, sn_handle *out) {
                     const dvec A = (d->fp_scheme == SN_FP_WFD) ? wfd_laplacian(N, mu, w) : mpd_laplacian(N, mu, w);
                     const dvec sa(K, key[3]), str(K, key[4]);
                     if (!build_fp_factors_coef(K, N, L, d->h + jobs[jb].second, sa.data(), str.data(), nullptr, mu, w,
-                                               A, mean_factors.at(key), 0, d->num_slabs))
+                                               A, mean_factors.at(key), 0, tree_slabs))
                         failed.store(1);
                 }
             };
@@ -1454,7 +1469,7 @@ sn_status sn_setup(const sn_problem_desc *d, void *stream, sn_handle *out) {
                                                                                : mpd_laplacian(N, m2, w2);
                                     if (!build_fp_factors(d->K[k], N, d->L[k], d->h + cc[k - bi], d->sigma_t + cc[k - bi],
                                                           d->sigma_s + ss[k - bi], m2, w2, A, group_factors[k - bi], 0,
-                                                          d->num_slabs))
+                                                          tree_slabs))
                                         failed.store(k);
                                 }
                             };

@@ -230,7 +230,7 @@ static int by_tree(const FPFactors &F, const dvec &diff, dvec &out) {
     return 0;
 }
 
-static int one(int K, int N, int L, int regions, int scheme, int slabs, bool fold, bool tree) {
+static int one(int K, int N, int L, int regions, int scheme, int slabs, bool fold) {
     dvec mu, w;
     gauss_legendre(N, mu, w);
     const dvec A = scheme == 0 ? wfd_laplacian(N, mu, w) : mpd_laplacian(N, mu, w);
@@ -251,10 +251,6 @@ static int one(int K, int N, int L, int regions, int scheme, int slabs, bool fol
     FPFactors E, F;
     CHECK(build(E, 0) && build(F, slabs));
     CHECK(E.tree.stages.empty() && !E.cellmats.empty());
-    if (!tree) {  // the eliminations' sizes
-        CHECK(F.tree.stages.empty() && F.cellmats == E.cellmats && F.EsrcT == E.EsrcT);
-        return 0;
-    }
     CHECK(!F.tree.stages.empty() && F.cellmats.empty() && F.EsrcT.empty());
     CHECK(F.chunk == E.chunk && F.nchunks == E.nchunks && F.seg_begin == E.seg_begin && F.seg_type == E.seg_type);
     std::mt19937 rng(K * 1000 + N);
@@ -278,26 +274,40 @@ static int one(int K, int N, int L, int regions, int scheme, int slabs, bool fol
 int main() {
     struct Case {
         int K, N, L, regions, scheme, slabs;
-        bool fold, tree;
+        bool fold;
     };
     // no level, one, a ragged last node, one chunk at its largest and past it;
     // two to five stages; passes cut by regions; column tiles below, at and
     // past 16; no two cells alike; many slabs; both sides of the sizes that
     // keep the eliminations
     const Case cases[] = {
-        {1, 2, 0, 1, 0, 1, true, true},      {2, 2, 1, 2, 1, 1, true, true},     {1, 16, 15, 1, 0, 4, false, true},
-        {3, 4, 3, 1, 1, 1, true, true},      {5, 2, 1, 2, 0, 1, true, true},     {17, 16, 15, 1, 0, 1, false, true},
-        {33, 18, 6, 4, 1, 1, true, true},    {64, 8, 7, 64, 0, 1, true, true},   {255, 8, 7, 1, 0, 1, true, true},
-        {256, 8, 7, 1, 0, 1, true, true},    {257, 8, 4, 1, 1, 1, true, true},   {257, 8, 4, 3, 1, 64, true, true},
-        {515, 24, 15, 5, 1, 1, true, true},  {515, 24, 15, 5, 1, 32, true, true}, {300, 10, 9, 300, 0, 1, true, true},
-        {1100, 6, 5, 4, 0, 1, true, true},   {4097, 4, 3, 2, 0, 1, true, true},  {20000, 2, 1, 3, 0, 1, true, true},
-        {140000, 2, 0, 1, 0, 1, false, true}, {70, 34, 33, 70, 0, 2, true, true}, {130, 64, 40, 3, 0, 1, true, true},
-        {200, 64, 63, 1, 0, 256, false, true}, {40, 66, 65, 1, 1, 1, true, true}, {36, 112, 111, 2, 0, 1, true, true},
-        {40, 128, 127, 2, 0, 1, true, true}, {64, 114, 20, 1, 0, 1, true, true}, {65, 114, 20, 1, 0, 1, true, false},
-        {66, 128, 9, 3, 0, 1, true, false},  {66, 128, 9, 4, 0, 1, true, true},  {18, 256, 255, 2, 1, 1, true, true},
+        {1, 2, 0, 1, 0, 1, true},      {2, 2, 1, 2, 1, 1, true},     {1, 16, 15, 1, 0, 4, false},
+        {3, 4, 3, 1, 1, 1, true},      {5, 2, 1, 2, 0, 1, true},     {17, 16, 15, 1, 0, 1, false},
+        {33, 18, 6, 4, 1, 1, true},    {64, 8, 7, 64, 0, 1, true},   {255, 8, 7, 1, 0, 1, true},
+        {256, 8, 7, 1, 0, 1, true},    {257, 8, 4, 1, 1, 1, true},   {257, 8, 4, 3, 1, 64, true},
+        {515, 24, 15, 5, 1, 1, true},  {515, 24, 15, 5, 1, 32, true}, {300, 10, 9, 300, 0, 1, true},
+        {1100, 6, 5, 4, 0, 1, true},   {4097, 4, 3, 2, 0, 1, true},  {20000, 2, 1, 3, 0, 1, true},
+        {140000, 2, 0, 1, 0, 1, false}, {70, 34, 33, 70, 0, 2, true}, {130, 64, 40, 3, 0, 1, true},
+        {200, 64, 63, 1, 0, 256, false}, {20, 34, 33, 2, 0, 1, true}, {50, 80, 70, 3, 0, 2, true},
+        {40, 66, 65, 1, 1, 1, true},   {36, 104, 103, 2, 0, 1, true}, {40, 128, 40, 2, 0, 1, true},
+        {66, 114, 20, 1, 0, 1, false}, {20, 130, 9, 1, 0, 1, true},  {9, 256, 255, 2, 1, 1, true},
     };
+    // the handles that keep the eliminations: cells, widths and runs at their
+    // ends, one slab, several, and of two padded widths
+    auto keeps = [](std::vector<FPSlabShape> v) { return fp_keeps_eliminations(v); };
+    CHECK(!keeps({}) && keeps({{65, 106, 1}}) && !keeps({{64, 106, 1}}) && !keeps({{65, 104, 1}}) && !keeps({{65, 130, 1}}));
+    CHECK(keeps({{700, 98, 2}}) && !keeps({{701, 98, 2}}) && !keeps({{100, 96, 2}}) && keeps({{100, 126, 3}}) && !keeps({{100, 124, 3}}));
+    CHECK(!keeps({{100, 128, 4}}) && !keeps({{200, 128, 200}}));
+    CHECK(keeps({{300, 128, 1}, {300, 106, 1}}) && !keeps({{300, 128, 1}, {301, 106, 1}}) && !keeps({{30, 128, 1}, {30, 104, 1}}));
+    CHECK(keeps({{500, 66, 2}, {500, 128, 1}}) && !keeps({{500, 66, 2}, {501, 128, 1}}) && keeps({{40, 80, 8}, {30, 70, 1}}) && !keeps({{40, 80, 9}, {30, 70, 1}}));
+    CHECK(keeps({{800, 50, 4}, {800, 64, 4}}) && !keeps({{800, 50, 3}, {800, 64, 3}}) && !keeps({{801, 50, 4}, {800, 64, 4}}) && !keeps({{80, 48, 8}, {80, 64, 8}}));
+    CHECK(!keeps({{80, 64, 8}, {80, 66, 8}}) && !keeps({{80, 128, 2}, {80, 130, 2}}));
+    CHECK(!keeps({{2000000000, 128, 2}, {2000000000, 128, 2}, {2000000000, 128, 2}}));
+    const double w[] = {1, 1, 2, 2, 1, 1}, t[] = {3, 3, 3, 3, 3, 4}, f[] = {1, 2, 1, 2, 1, 2, 1, 3, 1, 3, 1, 3};
+    CHECK(fp_runs(6, 2, w, nullptr, nullptr) == 3 && fp_runs(6, 2, w, t, nullptr) == 4 && fp_runs(6, 2, w, t, f) == 5);
+    CHECK(fp_runs(1, 2, w, t, f) == 1 && fp_runs(2, 2, w, t, f) == 1);
     for (const Case &c : cases)
-        if (one(c.K, c.N, c.L, c.regions, c.scheme, c.slabs, c.fold, c.tree)) {
+        if (one(c.K, c.N, c.L, c.regions, c.scheme, c.slabs, c.fold)) {
             std::fprintf(stderr, "K=%d N=%d L=%d regions=%d slabs=%d\n", c.K, c.N, c.L, c.regions, c.slabs);
             return 1;
         }
