@@ -42,7 +42,8 @@ TRAFFIC_SETS = {
 }
 # kernels each counter summary covers
 SET_KERNELS = {
-    "fpsa": ("sweep_aggregate", "sweep_scan", "sweep_apply", "fp_tree_up", "fp_tree_update", "exit_flux"),
+    "fpsa": ("sweep_aggregate", "sweep_scan", "sweep_apply", "fp_tree_up", "fp_tree_mid", "fp_tree_update",
+             "exit_flux"),
     "batch": ("sweep_batch_dm", "sweep_batch_f32", "src_batch_p<128>", "mom_batch_p<128>", "src_batch_p<64>",
               "mom_batch_p<64>", "src_batch_p<32>", "mom_batch_p<32>", "fused_scan",
               *(f"fused_{k}{s}<{w}>" for s in ("", "_sp") for w in (128, 64, 32) for k in ("aggregate", "apply"))),
@@ -50,11 +51,12 @@ SET_KERNELS = {
 # launches per iteration of each fused pass instance on the 4096-slab batch
 # (the 32-wide kernels also run the N = 16 class)
 FUSED_LAUNCHES = {128: 1, 64: 1, 32: 2}
-# substrings of the rocprofv3 kernel names of the timed kernel identities
-# (the tree's launches differ in their mode bits: leaves 1, up 2, root 4,
+# substrings of the rocprofv3 kernel names of the timed kernel identities (a
+# tuple: of several kernels; the tree's launches differ in their mode bits: leaves 1, up 2, root 4,
 # down 8, update 16)
 ROCPROF_NAME = {"sweep_aggregate": "snfpsa::sweep_aggregate", "sweep_scan": "snfpsa::sweep_scan_carry",
                 "sweep_apply": "snfpsa::sweep_apply", "fp_tree_up": "snfpsa::fpt_kernel<3,",
+                "fp_tree_mid": ("snfpsa::fpt_kernel<2,", "snfpsa::fpt_kernel<14,", "snfpsa::fpt_kernel<8,"),
                 "fp_tree_update": "snfpsa::fpt_kernel<24,", "exit_flux": "snfpsa::exit_flux",
                 "sweep_batch_dm": "snfpsa::sweep_batch_dm", "sweep_batch_f32": "snfpsa::sweep_batch_f32",
                 # persistent FP32 class GEMMs of the batched solve (<32> also runs the W = 16 classes)
@@ -105,28 +107,54 @@ def read_traffic_summary(kernel: str, which: str = "fpsa"):
     return float(v) if v is not None else None
 
 
-def algorithmic_bytes_per_iteration(K, N, L1):
+def algorithmic_bytes_per_iteration(K, N, L1, stages):
     """Bytes each kernel must move per FPSA iteration (FP64), by kernel name,
     with the number of launches of that kernel per iteration.  The workload's
     sweeps carry the scattering source and the moments (fused path); its
-    correction runs on the doubling tree.
+    correction runs on the doubling tree cut into `stages`
+    (paper_1907_13013_amd.diag_fp_tree; at least two).
 
     sweep_aggregate  phi and the external source in, the source q out (the
                      tile scan itself works on the tile in LDS)
     sweep_apply      q in, the half-step moments out
     fp_tree_up       phi_half and phi_old in, the interfaces' zero-inflow
                      values out
+    fp_tree_mid      the ascents and descents between and the root: per later
+                     stage its interfaces in and out (the root), or in, the
+                     zero-inflow values out and in again and the values out
     fp_tree_update   phi_half, phi_old and the interfaces in, phi_new out
-    The launches between (fp_tree_mid) work on the chunks' ends only, and the
-    matrices and tables every block reads come from cache: not counted.
+    The matrices and tables every block reads come from cache: not counted
+    (so fp_tree_mid, a chain of dependent levels in few blocks, is far below
+    any share of the bandwidth).
     """
     b = 8
+    mid = sum((2 if i == len(stages) - 1 else 4) * (s["n"] + 1) * N for i, s in enumerate(stages) if i)
     return {
         "sweep_aggregate": (b * (2 * K * L1 + 4 * K * N), 1),
         "sweep_apply": (b * (2 * K * N + 2 * K * L1), 1),
         "fp_tree_up": (b * (4 * K * L1 + K * N), 1),
+        "fp_tree_mid": (b * mid, 2 * len(stages) - 3),
         "fp_tree_update": (b * (6 * K * L1 + K * N), 1),
     }
+
+
+def rooflines(timing, per_iter):
+    """Every kernel of the iteration (algorithmic_bytes_per_iteration) that was
+    timed, {name: (launches, total ms)}, against the HBM roofline, and the name
+    of the one with the largest total time."""
+    kernels = {}
+    for name, (launches, total_ms) in timing.items():
+        if not launches or name not in per_iter:
+            continue
+        bytes_iter, launches_iter = per_iter[name]
+        per_launch = bytes_iter / launches_iter
+        avg_ms = total_ms / launches
+        achieved = per_launch / (avg_ms * 1e-3) / 1e9
+        kernels[name] = {"bound": "latency" if name == "fp_tree_mid" else "hbm", "kernel": name, "achieved": achieved,
+                         "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
+                         "traffic": read_traffic_summary(name), "avg_launch_us": avg_ms * 1e3,
+                         "algorithmic_bytes_per_launch": per_launch, "total_ms": total_ms}
+    return kernels, max(kernels, key=lambda k: kernels[k]["total_ms"]) if kernels else None
 
 
 def copy_probe(mib: int) -> int:
@@ -186,8 +214,9 @@ def summarize_profiles(fetch_dir, write_dir, copy_fetch_dir, copy_write_dir, cop
     for kid, sub in ROCPROF_NAME.items():
         if kid not in SET_KERNELS[which]:
             continue
-        fv = [x[2] for x in fetch if sub in x[0]]
-        wv = [x[2] for x in write if sub in x[0]]
+        subs = (sub,) if isinstance(sub, str) else sub
+        fv = [x[2] for x in fetch if any(t in x[0] for t in subs)]
+        wv = [x[2] for x in write if any(t in x[0] for t in subs)]
         if not fv or not wv:
             continue
         fk, wk = sum(fv) / len(fv), sum(wv) / len(wv)
@@ -901,23 +930,9 @@ def main() -> int:
     torch.cuda.synchronize()
     kt = S.kernel_timing()
     S.set_kernel_timing(False)
-    per_iter = algorithmic_bytes_per_iteration(K, N, L1)
-    # every kernel of the iteration against the HBM roofline, each GEMM
-    # instance on its own; the dominant one (largest total time) is the line's
-    # roofline
-    kernels = {}
-    for name, (launches, total_ms) in kt.items():
-        if not launches or name not in per_iter:
-            continue
-        bytes_iter, launches_iter = per_iter[name]
-        per_launch = bytes_iter / launches_iter
-        avg_ms = total_ms / launches
-        achieved = per_launch / (avg_ms * 1e-3) / 1e9
-        kernels[name] = {"bound": "hbm", "kernel": name, "achieved": achieved, "peak": HBM_PEAK_GBS,
-                         "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": read_traffic_summary(name),
-                         "avg_launch_us": avg_ms * 1e3, "algorithmic_bytes_per_launch": per_launch,
-                         "total_ms": total_ms}
-    dom = max(kernels, key=lambda k: kernels[k]["total_ms"]) if kernels else None
+    # the dominant kernel (largest total time) is the line's roofline
+    stages = snfpsa.diag_fp_tree(K, N, L1 - 1, prob.h, prob.sigma_t, prob.sigma_s, args.scheme)
+    kernels, dom = rooflines(kt, algorithmic_bytes_per_iteration(K, N, L1, stages))
     out["roofline"] = kernels.get(dom)
     out["roofline_per_kernel"] = {k: {"frac": v["frac"], "achieved": v["achieved"], "avg_launch_us": v["avg_launch_us"],
                                       "traffic": v["traffic"]} for k, v in kernels.items()}

@@ -50,6 +50,14 @@ sn_status sn_diag_fp_info(sn_diag_fp p, int32_t *info);
 sn_status sn_diag_fp_get(sn_diag_fp p, int32_t which, void *dst);
 sn_status sn_diag_fp_free(sn_diag_fp p);
 
+/* The doubling tree of a slab, one of so many of its kind in a handle, as
+ * sn_setup cuts it into launches.  info[0] = stages, then per stage (at most
+ * five) the leaves, leaves per chunk, chunks, levels and distinct node
+ * matrices (an N x 2N and an N x N each); 0 stages: the slab keeps the
+ * eliminations.  info: 26 entries. */
+sn_status sn_diag_fp_tree(int32_t K, int32_t N, int32_t L, const double *h, const double *sigma_t,
+                          const double *sigma_s, int32_t scheme, int32_t slabs, int32_t *info);
+
 /* The 256-wide classes of a batched (SN_F32 / SN_BF16X3) handle run the
  * solve's source and moments from BF16 pieces where the device can hold
  * those kernels.  enable = 0 takes them as not held, so that the kernels

@@ -43,7 +43,7 @@ EXPORTS = ["sn_setup", "sn_destroy", "sn_last_error", "sn_sweep", "sn_scatter_so
            "sn_set_kernel_timing",
            "sn_get_kernel_timing",
            "sn_diag_quadrature", "sn_diag_laplacian", "sn_diag_fp_factor", "sn_diag_fp_info",
-           "sn_diag_fp_get", "sn_diag_fp_free", "sn_diag_set_piece_gemms"]
+           "sn_diag_fp_get", "sn_diag_fp_free", "sn_diag_fp_tree", "sn_diag_set_piece_gemms"]
 
 
 class SnError(RuntimeError):
@@ -109,6 +109,7 @@ def load_library():
     lib.sn_diag_fp_info.argtypes = [vp, vp]
     lib.sn_diag_fp_get.argtypes = [vp, i32, vp]
     lib.sn_diag_fp_free.argtypes = [vp]
+    lib.sn_diag_fp_tree.argtypes = [i32, i32, i32, vp, vp, vp, i32, i32, vp]
     lib.sn_diag_set_piece_gemms.argtypes = [vp, i32]
     for name in EXPORTS:
         if name not in ("sn_last_error",):
@@ -557,3 +558,15 @@ def diag_fp_factors(K, N, L, h, sigma_t, sigma_s, scheme: str = "wfd", chunk: in
         return out
     finally:
         lib.sn_diag_fp_free(p)
+
+
+def diag_fp_tree(K, N, L, h, sigma_t, sigma_s, scheme: str = "wfd", slabs: int = 1) -> list:
+    """The stages of a slab's doubling tree (sn_diag_fp_tree): dicts of n, c,
+    chunks, levels, classes; empty where the slab keeps the eliminations."""
+    lib = load_library()
+    a = [np.ascontiguousarray(x, dtype=np.float64) for x in (h, sigma_t, sigma_s)]
+    info = np.zeros(26, dtype=np.int32)
+    _check(lib.sn_diag_fp_tree(K, N, L, a[0].ctypes.data, a[1].ctypes.data, a[2].ctypes.data, SCHEMES[scheme], slabs,
+                               info.ctypes.data))
+    return [dict(zip(("n", "c", "chunks", "levels", "classes"), (int(x) for x in info[1 + 5 * i:6 + 5 * i])))
+            for i in range(info[0])]

@@ -2594,4 +2594,35 @@ sn_status sn_diag_fp_free(sn_diag_fp p) {
     return SN_OK;
 }
 
+sn_status sn_diag_fp_tree(int32_t K, int32_t N, int32_t L, const double *h, const double *sigma_t,
+                          const double *sigma_s, int32_t scheme, int32_t slabs, int32_t *info) {
+    if (!info || !h || !sigma_t || !sigma_s || K < 1 || N < 2 || N % 2 || L < 0 || L >= N || slabs < 1)
+        return fail(SN_E_INVALID, "bad arguments");
+    try {
+        dvec m, ww;
+        gauss_legendre(N, m, ww);
+        const dvec A = scheme == SN_FP_WFD ? wfd_laplacian(N, m, ww) : mpd_laplacian(N, m, ww);
+        const std::vector<FPSlabShape> shapes((size_t)slabs, FPSlabShape{K, N, fp_runs(K, L + 1, h, sigma_t, sigma_s)});
+        FPFactors F;
+        if (!build_fp_factors(K, N, L, h, sigma_t, sigma_s, m, ww, A, F, 0, fp_keeps_eliminations(shapes) ? 0 : slabs))
+            return fail(SN_E_INVALID, "singular Fokker-Planck cell block");
+        std::fill(info, info + 1 + 5 * kTreeMaxStages, 0);
+        info[0] = (int32_t)F.tree.stages.size();
+        for (size_t i = 0; i < F.tree.stages.size(); ++i) {
+            const FPTreeStage &s = F.tree.stages[i];
+            std::vector<int> cls;
+            for (int p = 0; p < s.chunks; ++p) {
+                const int *lv = &F.tree.lv[(size_t)F.tree.chunk_list[s.first_chunk + p] * kTreeLv];
+                for (int q = lv[1]; q < lv[s.levels + 1]; ++q) cls.push_back(F.tree.passes[q].cls);
+            }
+            std::sort(cls.begin(), cls.end());
+            const int v[5] = {s.n, s.c, s.chunks, s.levels, (int)(std::unique(cls.begin(), cls.end()) - cls.begin())};
+            std::copy(v, v + 5, info + 1 + 5 * i);
+        }
+    } catch (const std::bad_alloc &) {
+        return fail(SN_E_NOMEM, "host allocation failed");
+    }
+    return SN_OK;
+}
+
 }  // extern "C"
