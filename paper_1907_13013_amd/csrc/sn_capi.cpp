@@ -1422,7 +1422,6 @@ sn_status sn_setup(const sn_problem_desc *d, void *stream, sn_handle *out) {
                     if (mean) fp_cache.emplace(mean_key[bi], bi);
                     if (!F.tree.stages.empty()) {
                         b.tstages = F.tree.stages;
-                        b.tstages = F.tree.stages;
                         b.tfrag = H->upload(F.tree.frag, st);
                         b.trecs = H->upload(F.tree.records, st);
                     } else {
@@ -1501,39 +1500,26 @@ sn_status sn_setup(const sn_problem_desc *d, void *stream, sn_handle *out) {
         H->build_exit_tables(d, st);
         // slots: one per concurrently iterated slab, within a memory budget
         {
-            const size_t per = sizeof(double) * (2 * ws_q + 3 * ws_phi + 2 * ws_s + 4 * ws_p + 2 * ws_e +
-                                                 2 * ws_part + 2 * ws_sub + 3 * ws_tile + 2 * ws_grp + ws_n);
+            const std::pair<double *Workspace::*, size_t> arrays[] = {
+                {&Workspace::q, ws_q}, {&Workspace::psi, ws_q},
+                {&Workspace::phiA, ws_phi}, {&Workspace::phiB, ws_phi}, {&Workspace::phi_half, ws_phi},
+                {&Workspace::s, ws_s}, {&Workspace::inflow, ws_s},
+                {&Workspace::pvec, ws_p}, {&Workspace::bvec, ws_p}, {&Workspace::fvec, ws_p}, {&Workspace::gvec, ws_p},
+                {&Workspace::e_fwd, ws_e}, {&Workspace::e_bwd, ws_e},
+                {&Workspace::part_f, ws_part}, {&Workspace::part_b, ws_part},
+                {&Workspace::subA, ws_sub}, {&Workspace::subB, ws_sub},
+                {&Workspace::tileA, ws_tile}, {&Workspace::tileB, ws_tile},
+                {&Workspace::nextA, ws_tile}, {&Workspace::nextB, ws_tile}, {&Workspace::carry, ws_tile},
+                {&Workspace::grpA, ws_grp}, {&Workspace::grpB, ws_grp}, {&Workspace::sweep_exit, ws_n}};
+            size_t per = 0;
+            for (const auto &a : arrays) per += a.second * sizeof(double);
             const size_t budget = (size_t)8 << 30;
             const int nslot = (int)std::max<size_t>(
                 1, std::min<size_t>({(size_t)kSlots, (size_t)d->num_slabs, budget / std::max<size_t>(per, 1)}));
             H->ws.resize(nslot);
             for (int g = 0; g < nslot; ++g) {
                 Workspace &W = H->ws[g];
-                W.q = H->dalloc<double>(ws_q);
-                W.psi = H->dalloc<double>(ws_q);
-                W.phiA = H->dalloc<double>(ws_phi);
-                W.phiB = H->dalloc<double>(ws_phi);
-                W.phi_half = H->dalloc<double>(ws_phi);
-                W.s = H->dalloc<double>(ws_s);
-                W.inflow = H->dalloc<double>(ws_s);
-                W.pvec = H->dalloc<double>(ws_p);
-                W.bvec = H->dalloc<double>(ws_p);
-                W.fvec = H->dalloc<double>(ws_p);
-                W.gvec = H->dalloc<double>(ws_p);
-                W.e_fwd = H->dalloc<double>(ws_e);
-                W.e_bwd = H->dalloc<double>(ws_e);
-                W.part_f = H->dalloc<double>(ws_part);
-                W.part_b = H->dalloc<double>(ws_part);
-                W.subA = H->dalloc<double>(ws_sub);
-                W.subB = H->dalloc<double>(ws_sub);
-                W.tileA = H->dalloc<double>(ws_tile);
-                W.tileB = H->dalloc<double>(ws_tile);
-                W.nextA = H->dalloc<double>(ws_tile);
-                W.nextB = H->dalloc<double>(ws_tile);
-                W.carry = H->dalloc<double>(ws_tile);
-                W.grpA = H->dalloc<double>(ws_grp);
-                W.grpB = H->dalloc<double>(ws_grp);
-                W.sweep_exit = H->dalloc<double>(ws_n);
+                for (const auto &a : arrays) W.*a.first = H->dalloc<double>(a.second);
                 if (g > 0) HIPCHK(hipStreamCreateWithFlags(&W.stream, hipStreamNonBlocking));
                 HIPCHK(hipEventCreateWithFlags(&W.done, hipEventDisableTiming));
             }
