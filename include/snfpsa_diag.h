@@ -3,9 +3,10 @@
  *
  * These calls expose what sn_setup computes on the host (quadrature, angular
  * Laplacians, and the factorised Fokker-Planck operator) so that the setup
- * can be checked on a machine without a GPU; the last one switches a kernel
- * variant off, for tests.  They launch no device work and no solver call
- * uses them.  All arrays are host memory, FP64 unless stated, row-major.
+ * can be checked on a machine without a GPU.  They launch no device work
+ * and no solver call uses them.  All arrays are host memory, FP64 unless
+ * stated, row-major.  (The last two, for tests on a GPU, choose paths that
+ * sn_setup and the solves take only in rare cases.)
  */
 #ifndef SNFPSA_DIAG_H
 #define SNFPSA_DIAG_H
@@ -64,6 +65,10 @@ sn_status sn_diag_fp_tree(int32_t K, int32_t N, int32_t L, const double *h, cons
  * that stand in for them can be tested; enable != 0 is the default.  Drops
  * the handle's captured graphs.  SN_E_STATE for SN_F64 handles. */
 sn_status sn_diag_set_piece_gemms(sn_handle h, int32_t enable);
+
+/* sn_setup with the Fokker-Planck eliminations for every slab, whatever its
+ * sizes: the path of a slab whose doubling tree cannot be built. */
+sn_status sn_diag_setup_eliminations(const sn_problem_desc *desc, void *stream, sn_handle *out);
 
 #ifdef __cplusplus
 }

@@ -43,7 +43,8 @@ EXPORTS = ["sn_setup", "sn_destroy", "sn_last_error", "sn_sweep", "sn_scatter_so
            "sn_set_kernel_timing",
            "sn_get_kernel_timing",
            "sn_diag_quadrature", "sn_diag_laplacian", "sn_diag_fp_factor", "sn_diag_fp_info",
-           "sn_diag_fp_get", "sn_diag_fp_free", "sn_diag_fp_tree", "sn_diag_set_piece_gemms"]
+           "sn_diag_fp_get", "sn_diag_fp_free", "sn_diag_fp_tree", "sn_diag_set_piece_gemms",
+           "sn_diag_setup_eliminations"]
 
 
 class SnError(RuntimeError):
@@ -110,6 +111,7 @@ def load_library():
     lib.sn_diag_fp_get.argtypes = [vp, i32, vp]
     lib.sn_diag_fp_free.argtypes = [vp]
     lib.sn_diag_fp_tree.argtypes = [i32, i32, i32, vp, vp, vp, i32, i32, vp]
+    lib.sn_diag_setup_eliminations.argtypes = [C.POINTER(ProblemDesc), vp, C.POINTER(vp)]
     lib.sn_diag_set_piece_gemms.argtypes = [vp, i32]
     for name in EXPORTS:
         if name not in ("sn_last_error",):

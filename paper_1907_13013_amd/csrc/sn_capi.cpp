@@ -1167,7 +1167,8 @@ extern "C" {
 
 const char *sn_last_error(void) { return g_err.c_str(); }
 
-sn_status sn_setup(const sn_problem_desc *d, void *stream, sn_handle *out) {
+// eliminations: every slab keeps them
+static sn_status setup_impl(const sn_problem_desc *d, void *stream, sn_handle *out, bool eliminations) {
     g_err.clear();
     if (!d || !out) return fail(SN_E_INVALID, "NULL descriptor or output pointer");
     *out = nullptr;
@@ -1255,7 +1256,7 @@ sn_status sn_setup(const sn_problem_desc *d, void *stream, sn_handle *out) {
                 c0 += K;
                 s0 += (int64_t)K * L1;
             }
-            if (!fp_keeps_eliminations(shapes)) tree_slabs = d->num_slabs;
+            if (!eliminations && !fp_keeps_eliminations(shapes)) tree_slabs = d->num_slabs;
         }
         // SN_FP_MEAN: per slab the width-weighted means of sigma_a and
         // sigma_tr, rounded to two significant digits; slabs with equal
@@ -1539,6 +1540,8 @@ sn_status sn_setup(const sn_problem_desc *d, void *stream, sn_handle *out) {
     *out = H;
     return SN_OK;
 }
+
+sn_status sn_setup(const sn_problem_desc *d, void *stream, sn_handle *out) { return setup_impl(d, stream, out, false); }
 
 sn_status sn_destroy(sn_handle h) {
     if (!h) return fail(SN_E_STATE, "NULL handle");
@@ -2505,6 +2508,10 @@ sn_status sn_diag_set_piece_gemms(sn_handle h, int32_t enable) {
     for (BatchData::GraphEntry &g : h->batch->graphs) (void)hipGraphExecDestroy(g.exec);
     h->batch->graphs.clear();
     return SN_OK;
+}
+
+sn_status sn_diag_setup_eliminations(const sn_problem_desc *d, void *stream, sn_handle *out) {
+    return setup_impl(d, stream, out, true);
 }
 
 sn_status sn_diag_quadrature(int32_t N, double *mu, double *w) {

@@ -119,3 +119,40 @@ def test_few_slabs(name, coef):
         assert np.abs(res[True][1][off:off + ref.size] - ref).max() < 1e-9 * np.abs(ref).max(), (p.K, p.N)
         off += ref.size
     S.close()
+
+
+# The path of a slab whose tree cannot be built, at every padded half-width
+# (2, 4, .. 128, below and at each), one region and several, slab by slab and
+# in batched launches.
+@pytest.mark.parametrize("N,L,K,regions", [
+    (2, 1, 30, 1), (4, 3, 41, 3), (6, 5, 25, 1), (8, 7, 64, 2), (12, 11, 33, 1), (16, 3, 50, 4), (20, 19, 40, 1),
+    (32, 31, 45, 2), (50, 20, 30, 1), (64, 63, 37, 3), (80, 79, 21, 1), (128, 127, 19, 2), (130, 129, 12, 1), (256, 100, 9, 2)])
+def test_every_width(N, L, K, regions, monkeypatch):
+    torch, snfpsa = _gpu()
+    print("eliminations, width", N, L, K, regions, flush=True)
+    lib = snfpsa.load_library()
+    monkeypatch.setattr(lib, "sn_setup", lib.sn_diag_setup_eliminations)
+    probs = [sw.random_slab(70 + N + i, K=K + 5 * i, N=N, L=L, regions=regions, kernel="hg", source="random", c_range=(0.8, 0.95))
+             for i in range(2)]
+    for S, group in ((snfpsa.SlabSolver(probs[:1], fp_scheme="mpd" if N == 12 else "wfd"), probs[:1]),
+                     (snfpsa.SlabSolver(probs, fp_scheme="wfd"), probs)):
+        scheme = S.fp_scheme
+        phs = [sw.random_vectors(10 + i, p.K, 2, L + 1) for i, p in enumerate(group)]
+        pos = [sw.random_vectors(20 + i, p.K, 2, L + 1) for i, p in enumerate(group)]
+        cat = lambda v: _dev(torch, np.concatenate([a.ravel() for a in v]))
+        out, names = _ran(S, lambda: S.fpsa_correct(cat(phs), cat(pos)))
+        assert "fp_chain" in names and not any(n.startswith("fp_tree") for n in names), names
+        q = cat([p.q for p in group])
+        r = S.solve("fpsa", tol=1e-11, max_iter=500, q_ext=q)
+        assert r["status"] == 0
+        got, phi, off = out.cpu().numpy(), r["phi"].cpu().numpy(), 0
+        for p, a, b, it in zip(group, phs, pos, r["iters"]):
+            ref, _ = oracle.fpsa_correct(p, a, b, scheme)
+            n = ref.size
+            d = got[off:off + n].reshape(ref.shape) - a
+            assert np.abs(d - (ref - a)).max() < 1e-10 * np.abs(ref - a).max(), (p.K, N)
+            z = oracle.solve(p, "fpsa", scheme, tol=1e-11, max_iter=500)
+            assert it == z["iters"]
+            assert np.abs(phi[off:off + n] - z["phi"].ravel()).max() < 1e-9 * np.abs(z["phi"]).max()
+            off += n
+        S.close()
