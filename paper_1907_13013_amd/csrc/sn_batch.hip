@@ -483,7 +483,7 @@ __global__ void __launch_bounds__(256) sweep_long_pass(BatchLongArgs a) {
 // block per chain, whose SCAN_WAVES waves fold the maps of a run of segments
 // each, then walk their runs from the runs before.  The maps are read 16 at a
 // time ahead of the fold.  One wave over all segments took 11 us for 128 of
-// them and grows with the count; 512 take 9.82 us.
+// them and grows with the count; 512 take 9.8 us.
 constexpr int SCAN_WAVES = 16;
 __global__ void __launch_bounds__(64 * SCAN_WAVES) sweep_long_scan(BatchLongArgs a) {
     __shared__ float2 maps[SCAN_WAVES][64];
