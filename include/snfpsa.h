@@ -63,14 +63,19 @@ typedef enum {
 /* Precision of a handle.
  *   SN_F64     everything in FP64 (sweeps, scattering GEMMs, FP correction).
  *   SN_F32     FP32 sweeps and q / psi storage; scattering source and moments
- *              on FP32 MFMA with FP32 accumulation; the quadrature / Legendre
+ *              on FP32 MFMA with FP32 accumulation, in the solves of many
+ *              sizes as six BF16 MFMA products of three BF16 pieces of each
+ *              operand, which round like FP32 (sn_fused_iteration, and slabs
+ *              of 130 to 256 angles; operands below 2^-110 lose digits there,
+ *              as their third pieces are subnormal); the quadrature / Legendre
  *              tables built in FP64 and rounded once.  phi passed in and out
  *              of every call is FP64; inside sn_solve the iterates are kept
  *              in FP32 and the stopping test is evaluated in FP64.  All slabs
  *              run batched (one launch per phase for the whole handle).
  *              Source iteration only.
  *   SN_BF16X3  as SN_F32 with the scattering source as split-BF16 products
- *              (hi*hi + hi*lo + lo*hi on BF16 MFMA, FP32 accumulation).      */
+ *              (hi*hi + hi*lo + lo*hi on BF16 MFMA, FP32 accumulation); the
+ *              moments of slabs of 130 to 256 angles from three pieces.      */
 typedef enum { SN_F64 = 0, SN_F32 = 1, SN_BF16X3 = 2 } sn_precision;
 /* SN_FP_NONE: no Fokker-Planck factorisation (source iteration only); used
  * for large batches whose factors would not fit. */
@@ -174,7 +179,8 @@ sn_status fpsa_correct(sn_handle h, const double *phi_half, const double *phi_ol
  * fpsa_correct, with the Fokker-Planck work vectors of each slab (its
  * source, both interface vectors, the chains' local values, the chunk end
  * values and carry partial sums: about (2 K N + 2 (K + 1) N + small) doubles
- * per slab) taken from a fixed scratch array of 64 MiB per device
+ * per slab, the same room where it runs on the doubling tree and uses less
+ * of it) taken from a fixed scratch array of 64 MiB per device
  * (resident from the library's load until the process ends, its address
  * resolved once per device by sn_setup) instead of the handle's workspace.
  * The call allocates nothing and records no per-kernel timing events.
@@ -358,7 +364,9 @@ sn_status sn_set_sweep_choice(sn_handle h, int32_t choice);
  * a second pass re-sweeps them.  At setup the segment length is chosen
  * among 512 (c = 0), 1024 (c = 1) and 2048 cells (c = 2) by timing one
  * warm-up and three sweeps of the handle's long slabs with each; the
- * fastest is kept.  *seg_cells receives its length (0 when the handle has
+ * fastest is kept.  With few segments in all (a slab or two) each is cut
+ * into up to eight equal parts, which then are the segments of the passes.
+ * *seg_cells receives the length before that cut (0 when the handle has
  * no such slab), ms[3] (nullable) the measured time per candidate (0
  * without long slabs).  Segment lengths change results by FP32 rounding
  * order only.  SN_E_STATE for SN_F64 handles. */
@@ -426,7 +434,8 @@ sn_status sn_set_graph_replay(sn_handle h, int32_t enable);
  * solution than the slab-by-slab solve's, by what that one had still to go
  * (of the order of tol).
  * With kernel timing off, one iteration is captured into a HIP graph (once
- * per source, method and boundary mode, four kept per handle) and replayed
+ * per source, method and boundary mode, whatever the tolerance, four kept per
+ * handle) and replayed
  * on a stream the handle owns, ordered after and before the caller's stream
  * by events.  The per-slab workspaces (about 3 phi + 4 psi values per
  * slab) are allocated on the first such solve; if they would exceed half
@@ -447,9 +456,11 @@ sn_status sn_set_kernel_timing(sn_handle h, int32_t enable);
 sn_status sn_get_kernel_timing(sn_handle h, int32_t kernel_id, const char **name,
                                int64_t *launches, double *total_ms);
 
-/* Layout of slab b (host helper, no device work): info[0..5] = K, N, L,
- * cells per chunk and number of chunks of the Fokker-Planck recurrences,
- * number of sweep tiles, cells per sweep tile (SN_F64 handles). */
+/* Layout of slab b (host helper, no device work): info[0..6] = K, N, L,
+ * cells per chunk and number of chunks of the Fokker-Planck recurrences
+ * (those that its eliminations take or, where the correction runs on the
+ * doubling tree, would take), number of sweep tiles, cells per sweep tile
+ * (SN_F64 handles). */
 sn_status sn_slab_info(sn_handle h, int32_t slab, int32_t *info);
 
 /* Sizes of the concatenated device arrays (host helper, no device work). */
