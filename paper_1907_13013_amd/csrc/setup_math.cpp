@@ -512,14 +512,22 @@ int fp_runs(int K, int L1, const double *h, const double *sigma_t, const double 
 
 // A wave waits for one batch of right operands while the next travels, so a
 // product of few rows is as long as its batches are many, and padding to whole
-// batches costs less than shorter ones.  us a correction in batches of 2, 4
-// and 8: K = 300, one type, N = 10 24.0 / 21.7 / 23.4, N = 20 28.1 / 26.3 /
-// 25.0, N = 34 39.4 / 34.8 / 35.5, N = 72 78 / 59 / 54, N = 104 108 / 84 / 77,
-// N = 130 317 / 186 / 132; 32 slabs of 500 cells, an iteration, N = 20 105 /
-// 100 / 101, N = 72 334 / 296 / 291, N = 104 516 / 447 / 438.
-int fp_tree_nb(int N) { return N <= 8 ? 2 : N <= 16 ? 4 : 8; }
-size_t fp_tree_ld(int N, int cols) {
-    const int kb = 4 * fp_tree_nb(N);
+// batches costs less than shorter ones, until the padding is work that fills
+// the part.  us a correction in batches of 2, 4 and 8: K = 300, one type,
+// N = 10 24.0 / 21.7 / 23.4, N = 20 28.1 / 26.3 / 25.0, N = 34 39.4 / 34.8 /
+// 35.5, N = 48 44 / 35.2 / 35.7, N = 72 78 / 59 / 54, N = 104 108 / 84 / 77,
+// N = 130 317 / 186 / 132.  Large batches, an iteration, 64 slabs of 300 cells:
+// N = 24 122 / 119 / 116, N = 40 199 / 182 / 209, N = 48 263 / 217 / 233, N = 72
+// 531 / 437 / 413; 32 of 2048: N = 24 185 / 194 / 192, N = 40 362 / 341 / 388,
+// N = 48 394 / 363 / 400, N = 72 986 / 872 / 852.
+int fp_tree_nb(int N, long long cells) {
+    if (N <= 8) return 2;
+    if (N <= 16) return 4;
+    if (N <= 24) return cells <= 32768 ? 8 : 2;
+    return N > 32 && N <= 48 ? 4 : 8;
+}
+size_t fp_tree_ld(int nb, int cols) {
+    const int kb = 4 * nb;
     return (size_t)(cols + kb - 1) / kb * kb + 1;
 }
 
@@ -539,13 +547,13 @@ dvec fp_tree_fragments(const double *B, int K, int cols, int nb) {
 
 // doubles of LDS of a chunk of c leaves: interface rows, the second set of
 // rows of a root chunk, and the moment-difference rows of a leaf stage
-static size_t tree_lds(int N, int L2, int c, bool leaf, bool root) {
-    return (size_t)(root ? 2 : 1) * (c + 1) * fp_tree_ld(N, N) + (leaf ? (size_t)c * fp_tree_ld(N, L2) : 0);
+static size_t tree_lds(int nb, int N, int L2, int c, bool leaf, bool root) {
+    return (size_t)(root ? 2 : 1) * (c + 1) * fp_tree_ld(nb, N) + (leaf ? (size_t)c * fp_tree_ld(nb, L2) : 0);
 }
 
 // Fragments and per-wave unit lists of a built tree.
 static bool tree_records(int N, int L2, const FPFactors &maps, FPTree &out) {
-    const int nb = fp_tree_nb(N), nt = maps.ntypes;
+    const int nb = out.nb, nt = maps.ntypes;
     const int ksN = (N + 4 * nb - 1) / (4 * nb) * nb, ksL = (L2 + 4 * nb - 1) / (4 * nb) * nb;
     const int ctN = (N + 15) / 16, ctU = (2 * N + 15) / 16, ctL = (L2 + 15) / 16;
     // fragment offsets, in blocks of 64 doubles
@@ -626,7 +634,7 @@ static bool tree_records(int N, int L2, const FPFactors &maps, FPTree &out) {
 // of level l's interfaces.
 static bool tree_stages(int K, int N, int L2, int slabs, const std::vector<int> &cls0,
                         const std::vector<std::vector<int>> &icls, FPTree &out) {
-    const int nb = fp_tree_nb(N), top = (int)icls.size() - 1;
+    const int nb = out.nb, top = (int)icls.size() - 1;
     const int ksN = (N + 4 * nb - 1) / (4 * nb) * nb, ksL = (L2 + 4 * nb - 1) / (4 * nb) * nb;
     const int ctN = (N + 15) / 16, ctU = (2 * N + 15) / 16, ctL = (L2 + 15) / 16;
     // a product of so many rows with ct column tiles over ks k-steps
@@ -641,7 +649,7 @@ static bool tree_stages(int K, int N, int L2, int slabs, const std::vector<int> 
         const int n = (int)(((size_t)K + ((size_t)1 << lo) - 1) >> lo), c = 1 << (hi - lo);
         const int chunks = (n + c - 1) / c, rows = std::min(c, n);
         if (rows > kTreeMaxRows || 2 * (hi - lo) + 2 > kTreeHdr) return -1.0;
-        if (tree_lds(N, L2, rows, leaf, root) * sizeof(double) > kTreeLdsBytes) return -1.0;
+        if (tree_lds(nb, N, L2, rows, leaf, root) * sizeof(double) > kTreeLdsBytes) return -1.0;
         double up = 0.0, down = 0.0, whole = 0.0;
         for (int p = 0; p < chunks; ++p) {
             double u = 0.0, d = 0.0;
@@ -676,7 +684,7 @@ static bool tree_stages(int K, int N, int L2, int slabs, const std::vector<int> 
         }
         const double rows_us = (double)rows * (N + (leaf ? 2 * L2 : 0)) * 8 * kTreeUsPerByte;
         // more chunks than CUs: rounds, which overlap where two blocks fit a CU
-        const bool two = tree_lds(N, L2, rows, leaf, root) * sizeof(double) <= kTreeLdsTwo;
+        const bool two = tree_lds(nb, N, L2, rows, leaf, root) * sizeof(double) <= kTreeLdsTwo;
         const double rounds = std::max(1.0, (double)chunks * slabs / kTreeCus * (two ? 0.7 : 1.0));
         return root ? kTreeUsPerLaunch + rounds * (whole + rows_us)
                     : 2 * kTreeUsPerLaunch + rounds * (up + down + 2 * rows_us);
@@ -721,6 +729,7 @@ bool build_fp_tree(int K, int N, int L, int slabs, const FPCellTypes &ct, const 
     const int NH = N / 2, L2 = 2 * (L + 1);
     const size_t M2 = (size_t)NH * NH, N2 = (size_t)N * N;
     out = FPTree();
+    out.nb = fp_tree_nb(N, (long long)slabs * K);
     const int ntypes = (int)ct.T.size();
     // node classes: operators (T, R, R', T') per class, classes of equal
     // child pairs shared

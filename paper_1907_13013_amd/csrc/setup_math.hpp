@@ -101,6 +101,7 @@ constexpr double kTreeUsPerLaunch = 4.5, kTreeUsPerLevel = 0.7, kTreeUsPerByte =
 constexpr int kTreeCus = 256;
 struct FPTree {
     std::vector<FPTreeStage> stages;  // empty: no tree
+    int nb = 0;                       // fp_tree_nb
     int nclasses = 0;
     dvec mats;                        // [nclasses]: up [N][2N], then down [N][N]
     std::vector<FPPass> passes;
@@ -115,8 +116,8 @@ struct FPTree {
     // tile << 16), one unit (pass, column tile) after the other
     std::vector<int> records;
 };
-int fp_tree_nb(int N);                // k-steps of 4 per batch of right operands
-size_t fp_tree_ld(int N, int cols);   // LDS row stride of left operands of so many columns
+int fp_tree_nb(int N, long long cells);  // k-steps of 4 per batch of right operands; cells: of all slabs
+size_t fp_tree_ld(int nb, int cols);     // LDS row stride of left operands of so many columns
 // [K][cols] in the kernels' fragment order (see FPTreeArgs)
 dvec fp_tree_fragments(const double *B, int K, int cols, int nb);
 

@@ -112,6 +112,7 @@ struct Slab {
     int chunk = 0, nchunks = 0;
     // doubling tree (no stages: the eliminations above)
     std::vector<FPTreeStage> tstages;
+    int tnb = 0;
     double *tfrag = nullptr;
     int *trecs = nullptr;
     // source maps without the cell's sigma_s (shared factorisations): the
@@ -547,8 +548,8 @@ std::vector<TreeLaunch> tree_launches(const Workspace &W, const Slab &b, const d
         a.N = b.N; a.L2 = 2 * b.L1;
         a.n = t.n; a.c = t.c; a.chunks = t.chunks; a.levels = t.levels;
         a.rows = std::min(t.c, t.n);
-        a.nb = fp_tree_nb(a.N);
-        a.lda = (int)fp_tree_ld(a.N, a.L2); a.ldy = (int)fp_tree_ld(a.N, a.N);
+        a.nb = b.tnb;
+        a.lda = (int)fp_tree_ld(a.nb, a.L2); a.ldy = (int)fp_tree_ld(a.nb, a.N);
         a.rcpN = (unsigned)((((uint64_t)1 << 32) + a.N - 1) / a.N);
         a.rcpL2 = (unsigned)((((uint64_t)1 << 32) + a.L2 - 1) / a.L2);
         a.frag = b.tfrag; a.recs = b.trecs + t.rec0; a.rec_stride = t.rec_stride;
@@ -1361,7 +1362,7 @@ static sn_status setup_impl(const sn_problem_desc *d, void *stream, sn_handle *o
                         b.EsrcT = o.EsrcT; b.PhisrcT = o.PhisrcT; b.PhiinfT = o.PhiinfT;
                         b.seg_begin = o.seg_begin; b.seg_type = o.seg_type;
                         b.chunk = o.chunk; b.nchunks = o.nchunks;
-                        b.tstages = o.tstages; b.tfrag = o.tfrag; b.trecs = o.trecs;
+                        b.tstages = o.tstages; b.tnb = o.tnb; b.tfrag = o.tfrag; b.trecs = o.trecs;
                         b.fold_ss = false;
                         shared = true;
                     }
@@ -1423,6 +1424,7 @@ static sn_status setup_impl(const sn_problem_desc *d, void *stream, sn_handle *o
                     if (mean) fp_cache.emplace(mean_key[bi], bi);
                     if (!F.tree.stages.empty()) {
                         b.tstages = F.tree.stages;
+                        b.tnb = F.tree.nb;
                         b.tfrag = H->upload(F.tree.frag, st);
                         b.trecs = H->upload(F.tree.records, st);
                     } else {

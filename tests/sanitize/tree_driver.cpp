@@ -83,7 +83,7 @@ static dvec eliminate(const FPFactors &F, const dvec &diff) {
 // The same by the tree's records.
 static int by_tree(const FPFactors &F, const dvec &diff, dvec &out) {
     const FPTree &T = F.tree;
-    const int K = F.K, N = F.N, NH = F.NH, L2 = 2 * (F.L + 1), nb = fp_tree_nb(N), KB = 4 * nb;
+    const int K = F.K, N = F.N, NH = F.NH, L2 = 2 * (F.L + 1), nb = F.tree.nb, KB = 4 * nb;
     const int ksN = (N + KB - 1) / KB * nb, ksL = (L2 + KB - 1) / KB * nb;
     const int ctN = (N + 15) / 16, ctU = (2 * N + 15) / 16, ctL = (L2 + 15) / 16;
     const int S = (int)T.stages.size();
@@ -98,7 +98,7 @@ static int by_tree(const FPFactors &F, const dvec &diff, dvec &out) {
         CHECK(s.n == n && s.c == 1 << s.levels && s.chunks == (n + s.c - 1) / s.c && (s.leaf != 0) == (i == 0));
         CHECK(std::min(s.c, s.n) <= kTreeMaxRows && 2 * s.levels + 2 <= kTreeHdr);
         const size_t rows = std::min(s.c, s.n), root = i == S - 1;
-        const size_t lds = (1 + root) * (rows + 1) * fp_tree_ld(N, N) + (s.leaf ? rows * fp_tree_ld(N, L2) : 0);
+        const size_t lds = (1 + root) * (rows + 1) * fp_tree_ld(nb, N) + (s.leaf ? rows * fp_tree_ld(nb, L2) : 0);
         CHECK(lds * sizeof(double) <= (160u << 10));
         CHECK(s.rec0 + (size_t)s.chunks * kTreeWaves * s.rec_stride <= T.records.size());
         CHECK(s.rec_stride >= kTreeHdr + 4 && (s.rec_stride - kTreeHdr) % 2 == 0 && s.rec_stride - kTreeHdr <= 2 * kTreeMaxUnits);
@@ -291,6 +291,7 @@ int main() {
         {200, 64, 63, 1, 0, 256, false}, {20, 34, 33, 2, 0, 1, true}, {50, 80, 70, 3, 0, 2, true},
         {40, 66, 65, 1, 1, 1, true},   {36, 104, 103, 2, 0, 1, true}, {40, 128, 40, 2, 0, 1, true},
         {66, 114, 20, 1, 0, 1, false}, {20, 130, 9, 1, 0, 1, true},  {9, 256, 255, 2, 1, 1, true},
+        {70, 20, 19, 3, 0, 400, true}, {70, 20, 19, 3, 0, 500, true}, {90, 46, 45, 2, 0, 1, true},
     };
     // the handles that keep the eliminations: cells, widths and runs at their
     // ends, one slab, several, and of two padded widths
